@@ -76,7 +76,7 @@ typedef struct cvf3_state cvf3_state;
 /* Workspace size for params p (L even, 2..CVF3_MAX_L; q 2..6; the rest as
  * for cvf_init) and the algorithms the chain will run (algo_mask:
  * CVF_ALGO_METROPOLIS | CVF_ALGO_SW).  Metropolis needs a few KB; SW adds
- * 4N bytes of link masks and 24N bytes of labels and needs 6N < 2^32
+ * 28N bytes of labelling state and needs 6N < 2^32
  * (L <= 894).  CVF_EINVAL on invalid parameters, mask or a NULL bytes. */
 int cvf3_workspace_bytes(const cvf_params *p, int algo_mask, size_t *bytes);
 
@@ -128,14 +128,12 @@ int cvf3_observables(cvf3_state *st, cvf3_obs *out, void *stream);
 
 /* Per-kernel HIP-event timing (off by default): enabling or disabling
  * clears the totals; times are collected when read.  Each launch records
- * its start/stop events on its own dispatch (the kernel's execution alone);
- * CVF3_K_SW_UNION and CVF3_K_SW_FLIP span their two and four launches with
- * events on the stream. */
+ * its start/stop events on its own dispatch (the kernel's execution alone). */
 #define CVF3_K_VOLUME 0     /* counter fold + volume move + pass order */
 #define CVF3_K_ETA    1     /* eta move over the checkerboard cubes    */
 #define CVF3_K_PASS   2     /* one arm-domain sigma pass               */
-#define CVF3_K_SW_BONDS 3   /* SW link masks                           */
-#define CVF3_K_SW_UNION 4   /* SW union-find over the links            */
+#define CVF3_K_SW_BONDS 3   /* SW links and components inside a tile   */
+#define CVF3_K_SW_UNION 4   /* SW union-find over tile-crossing links  */
 #define CVF3_K_SW_FLIP  5   /* SW cluster shift + recount              */
 #define CVF3_K_COUNT  6
 int cvf3_timing_enable(cvf3_state *st, int enable);

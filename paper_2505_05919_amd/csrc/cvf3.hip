@@ -12,10 +12,10 @@
 //                 of that arm moves once (the arm-domain partition of
 //                 Sec. II.C); a lane moves two x-adjacent cells, which share
 //                 one Philox block
-// A Swendsen-Wang step (Sec. II.D) replaces the passes by sw3_bonds_kernel
-// (link masks, cooperative links closed in registers), sw3_tile_union_kernel
-// (in-tile covalent links, LDS union-find), sw3_union_kernel (tile-crossing
-// links, global union-find), sw3_flip_kernel (cluster shifts) and a recount.
+// A Swendsen-Wang step (Sec. II.D) replaces the passes by sw3_tile_kernel
+// (links, components inside a tile), sw3_union_kernel (tile-crossing links,
+// global union-find over the tiles' face indices) and sw3_flip_kernel (cluster
+// shifts and the recount).
 // Layout: sigma[a*N + c], eta[d*N + c] (edge from c to its +d neighbour),
 // c = x + L*(y + L*z); arms 0:+x 1:-x 2:+y 3:-y 4:+z 5:-z.
 #include <hip/hip_runtime.h>
@@ -67,12 +67,16 @@ struct Lat3 {
     int64_t*   slots;         // [kAcc][kSlots]
     int64_t*   rc;            // [kRc][kSlots]
     const Tab3* tab;          // device copy
-    uint32_t*  mask;          // [N] SW link masks (NULL without SW)
-    uint32_t*  par;           // [6N] SW union-find parents, then labels
+    // Swendsen-Wang only (NULL without it); F plus nodes, see sw3_step.h
+    uint32_t*  par;           // [2F] parents of the tile-face nodes
+    uint32_t*  key;           // [2F] smallest flat index of a representative's component
+    uint16_t*  lroot;         // [6N] tile-local root of every bond index, or its component's face position
+    uint8_t*   edge;          // [F] old sigma facing a plus face, bit 7: the link there is active
     uint32_t L, N, h, q;
     uint32_t key0, key1;
     uint32_t pass;
     uint32_t quad;            // 1: L % 4 == 0, four cells per lane; 0: cell pairs
+    uint32_t eta_hb;          // 1: the eta move adds its change of N_HB_raw to the counters
     double   invL, invH, invQ4, Nd, beta, J, P, vHB, dv_max;
     int32_t  do_volume;
 };
@@ -355,7 +359,12 @@ __global__ __launch_bounds__(64) void vol3_kernel(Lat3 a, int mode)
     for (int i = 0; i < 6; ++i) s->order[i] = ord[i];
     s->t_cur = t;
     s->t_next = t_next + 1;
-    if (mode == kVolMet) s->met_att = matt0 + 6 * (int64_t)a.N;
+    if (mode == kVolMet) {
+        s->met_att = matt0 + 6 * (int64_t)a.N;
+    } else {                                       // the SW step ends with a full recount
+        s->n_hb_raw = 0;
+        s->n_coop = 0;
+    }
     s->eta_att = eatt0 + a.N / 4;
 }
 
@@ -399,7 +408,7 @@ __global__ __launch_bounds__(kBlock) void eta3_kernel(Lat3 a)
                 acc = thr == 0xFFFFFFFFu || w.y < thr;
             }
             if (acc) {
-                cnt[0] = dn;
+                cnt[0] = a.eta_hb ? dn : 0;
                 cnt[1] = 1;
                 const uint32_t neu = (~mask) & 0xFFFu;
                 if (neu != old) {
@@ -523,7 +532,7 @@ __global__ __launch_bounds__(kBlock) void eta3_pair_kernel(Lat3 a)
                 acc = thr == 0xFFFFFFFFu || w.y < thr;
             }
             if (!acc) continue;
-            cnt[0] += dn;
+            cnt[0] += a.eta_hb ? dn : 0;
             cnt[1] += 1;
             const uint32_t chg = neu ^ old;
             if (!chg) continue;
@@ -834,304 +843,7 @@ __global__ __launch_bounds__(kBlock) void pass3_kernel(Lat3 a)
     }
 }
 
-// ---------------------------------------------------------------------------
-// Swendsen-Wang on the cubic lattice (Sec. II.D).  Links of cell c, bit l of
-// its mask: l = 0..2 the covalent link of its +d edge (arm 2d of c with arm
-// 2d+1 of the +d neighbour; liquid and eta = 1 only; equal arms for
-// J_eff > 0, unequal for J_eff < 0), l = 3..17 the 15 cooperative pairs
-// (a, b), a < b, lexicographic (equal arms).  Link l uses word l mod 4 of
-// Philox(c, t, l / 4, SWB); bond iff word < 64-bit threshold.
-// Clusters by a lock-free union-find over the 6N bond indices: a link hooks
-// the larger of its two roots under the smaller (CAS on a root's own entry),
-// finds halve paths with plain stores of ancestors into non-roots only, so
-// parents only decrease and every component ends with its smallest index as
-// root -- the label the method's fixed point gives.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void sw3_bonds_kernel(Lat3 a)
-{
-    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
-    if (c >= a.N) return;
-    const uint32_t L = a.L, N = a.N, L2 = L * L;
-    const uint32_t t = (uint32_t)a.st->t_cur;
-    const int theta = a.st->theta;
-    uint32_t s[6];
-#pragma unroll
-    for (int b = 0; b < 6; ++b) s[b] = a.sigma[(size_t)b * N + c];
-    const uint32_t yz = udiv(c, L, a.invL);
-    const uint32_t x = c - yz * L;
-    const uint32_t z = udiv(yz, L, a.invL);
-    const uint32_t y = yz - z * L;
-    const uint32_t nbr[3] = {x == L - 1 ? c + 1 - L : c + 1, y == L - 1 ? c + L - L2 : c + L,
-                             c + L2 >= N ? c + L2 - N : c + L2};
-    uint32_t w[20];
-#pragma unroll
-    for (int b = 0; b < 5; ++b) {
-        const uint4 r = philox(c, t, (uint32_t)b, kSwb, a.key0, a.key1);
-        w[4 * b] = r.x;
-        w[4 * b + 1] = r.y;
-        w[4 * b + 2] = r.z;
-        w[4 * b + 3] = r.w;
-    }
-    const uint64_t ts = a.tab->sw_sigma, te = theta ? a.tab->sw_eff : 0;
-    const int sgn = a.tab->jeff_sign;
-    uint32_t m = 0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const bool eq = s[2 * d] == a.sigma[(size_t)(2 * d + 1) * N + nbr[d]];
-        const bool allowed = theta && a.eta[(size_t)d * N + c] != 0;
-        const bool want = sgn > 0 ? eq : (sgn < 0 ? !eq : false);
-        if (allowed && want && (uint64_t)w[d] < te) m |= 1u << d;
-    }
-    int l = 0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int j = i + 1; j < 6; ++j, ++l)
-            if (s[i] == s[j] && (uint64_t)w[3 + l] < ts) m |= 1u << (3 + l);
-    a.mask[c] = m;
-    // The cooperative links join arms of this cell only: their components
-    // (transitive closure of the six arms' adjacency, Warshall's order) are
-    // resolved here, each arm's parent set to the smallest arm of its
-    // component -- the smallest flat index, since arm a of c is a N + c.
-    uint32_t comp[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) comp[i] = 1u << i;
-    l = 0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int j = i + 1; j < 6; ++j, ++l)
-            if ((m >> (3 + l)) & 1u) {
-                comp[i] |= 1u << j;
-                comp[j] |= 1u << i;
-            }
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-#pragma unroll
-        for (int i = 0; i < 6; ++i)
-            if ((comp[i] >> k) & 1u) comp[i] |= comp[k];
-#pragma unroll
-    for (int b = 0; b < 6; ++b) a.par[(size_t)b * N + c] = (uint32_t)(__builtin_ctz(comp[b])) * N + c;
-}
-
-__device__ __forceinline__ uint32_t uf_find(uint32_t* par, uint32_t x)
-{
-    uint32_t p = par[x];
-    while (p != x) {
-        const uint32_t g = par[p];
-        if (g != p) par[x] = g;                            // halve: an ancestor into a non-root
-        x = p;
-        p = g;
-    }
-    return x;
-}
-
-__device__ __forceinline__ void uf_unite(uint32_t* par, uint32_t u, uint32_t v)
-{
-    while (true) {
-        u = uf_find(par, u);
-        v = uf_find(par, v);
-        if (u == v) return;
-        if (u < v) {
-            const uint32_t tmp = u;
-            u = v;
-            v = tmp;
-        }
-        const uint32_t old = atomicCAS(par + u, u, v);    // hook the larger root
-        if (old == u) return;
-        u = old;
-    }
-}
-
-// Tile phase (L % 8 == 0): one workgroup per TX x TY x TZ cells.  Its 6 T
-// bond indices get local indices a T + lx + TX (ly + TY lz), which order
-// them as their flat indices a N + c do, so the same rule (hook the larger
-// root under the smaller, CAS in LDS) leaves every in-tile component rooted
-// at its smallest flat index.  Covalent links inside the tile are united
-// here; each bond index's global parent becomes its in-tile root, and only
-// links that cross a tile face remain for sw3_union_kernel.
-__device__ __forceinline__ uint32_t lds_find(uint32_t* lp, uint32_t x)
-{
-    uint32_t p = lp[x];
-    while (p != x) {
-        const uint32_t g = lp[p];
-        if (g != p) lp[x] = g;
-        x = p;
-        p = g;
-    }
-    return x;
-}
-
-__device__ __forceinline__ void lds_unite(uint32_t* lp, uint32_t u, uint32_t v)
-{
-    while (true) {
-        u = lds_find(lp, u);
-        v = lds_find(lp, v);
-        if (u == v) return;
-        if (u < v) {
-            const uint32_t tmp = u;
-            u = v;
-            v = tmp;
-        }
-        const uint32_t old = atomicCAS(lp + u, u, v);
-        if (old == u) return;
-        u = old;
-    }
-}
-
-template <int TX, int TY, int TZ>
-__global__ __launch_bounds__(TX * TY * TZ) void sw3_tile_union_kernel(Lat3 a)
-{
-    constexpr uint32_t T = TX * TY * TZ;
-    __shared__ uint32_t lp[6 * T];
-    const uint32_t L = a.L, N = a.N;
-    const uint32_t tx = L / TX, ty = L / TY;
-    // Workgroups are dealt to the eight XCDs in turn, and a tile's row of a
-    // plane is TX bytes, a fraction of an L2 line: the j-th workgroup of an
-    // XCD takes tile 8 (8 (j / 8) + xcd) + j % 8, so each XCD works on runs of
-    // 8 tiles along x that share their lines (the last n % 64 tiles keep
-    // their place).
-    const uint32_t nt = gridDim.x;
-    uint32_t b = blockIdx.x;
-    if (b < nt - nt % 64) {
-        const uint32_t xcd = b % 8, j = b / 8;
-        b = ((j / 8) * 8 + xcd) * 8 + j % 8;
-    }
-    const uint32_t bx = b % tx, by = (b / tx) % ty, bz = b / (tx * ty);
-    const uint32_t t = threadIdx.x, lx = t % TX, ly = (t / TX) % TY, lz = t / (TX * TY);
-    const uint32_t c = (TX * bx + lx) + L * ((TY * by + ly) + L * (TZ * bz + lz));
-    // in-cell roots from the bonds kernel: parent of arm k is arm r of the same cell
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const uint32_t r = a.par[(size_t)k * N + c] / N;
-        lp[k * T + t] = r * T + t;
-    }
-    __syncthreads();
-    const uint32_t m = a.mask[c] & 7u;
-    if ((m & 1u) && lx < TX - 1) lds_unite(lp, 0 * T + t, 1 * T + t + 1);
-    if ((m & 2u) && ly < TY - 1) lds_unite(lp, 2 * T + t, 3 * T + t + TX);
-    if ((m & 4u) && lz < TZ - 1) lds_unite(lp, 4 * T + t, 5 * T + t + TX * TY);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        uint32_t x = k * T + t, q = lp[x];
-        while (q != x) {                                   // read-only: lp is not written any more
-            x = q;
-            q = lp[x];
-        }
-        const uint32_t rt = x % T, ra = x / T;
-        const uint32_t rc = (TX * bx + rt % TX) + L * ((TY * by + (rt / TX) % TY) + L * (TZ * bz + rt / (TX * TY)));
-        a.par[(size_t)k * N + c] = ra * N + rc;
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void sw3_union_kernel(Lat3 a, uint32_t tx_, uint32_t ty_, uint32_t tz_)
-{
-    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
-    if (c >= a.N) return;
-    uint32_t m = a.mask[c] & 7u;                        // covalent links; cooperative ones are resolved
-    if (!m) return;
-    const uint32_t L = a.L, N = a.N, L2 = L * L;
-    {
-        const uint32_t yz = udiv(c, L, a.invL);
-        const uint32_t x = c - yz * L;
-        const uint32_t z = udiv(yz, L, a.invL);
-        const uint32_t y = yz - z * L;
-        const uint32_t nbr[3] = {x == L - 1 ? c + 1 - L : c + 1, y == L - 1 ? c + L - L2 : c + L,
-                                 c + L2 >= N ? c + L2 - N : c + L2};
-        if (tx_) {                                        // in-tile links were united by the tile phase
-            if (x % tx_ != tx_ - 1) m &= ~1u;
-            if (y % ty_ != ty_ - 1) m &= ~2u;
-            if (z % tz_ != tz_ - 1) m &= ~4u;
-        }
-        // A link whose two ends have the same parents as the active link of
-        // the same direction one cell lower along another axis (no wrap) is
-        // already implied: each parent is an ancestor of its end, ancestors
-        // stay ancestors, so equal parents mean the same two components, and
-        // the lower link is united or itself implied by a link lower still.
-        // On a percolating cluster most face links repeat a neighbour's pair.
-        const uint32_t crd[3] = {x, y, z}, stride[3] = {1u, L, L2};
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            if (!((m >> d) & 1u)) continue;
-            const uint32_t u = (2 * d) * N + c, v = (2 * d + 1) * N + nbr[d];
-            const uint32_t pu = a.par[u], pv = a.par[v];
-            bool implied = false;
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-                if (e == d || crd[e] == 0) continue;
-                const uint32_t cl = c - stride[e];
-                if (!((a.mask[cl] >> d) & 1u)) continue;
-                if (a.par[(2 * d) * N + cl] == pu && a.par[(2 * d + 1) * N + nbr[d] - stride[e]] == pv) implied = true;
-            }
-            if (!implied) uf_unite(a.par, u, v);
-        }
-    }
-}
-
-// Every bond index gets its root (the smallest index of its cluster), and
-// shifts by pick(word 0 of Philox(root, t, 0, SWF), q), NONE -> 0.
-// Workgroup 0 also clears the recount accumulators for the recount that
-// follows (nothing in this launch reads them).
-__global__ __launch_bounds__(kBlock) void sw3_flip_kernel(Lat3 a)
-{
-    if (blockIdx.x == 0)
-        for (uint32_t j = threadIdx.x; j < (uint32_t)(kRc * kSlots); j += kBlock) a.rc[j] = 0;
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= 6 * a.N) return;
-    const uint32_t r = uf_find(a.par, i);
-    const uint32_t t = (uint32_t)a.st->t_cur;
-    const uint4 w = philox(r, t, 0u, kSwf, a.key0, a.key1);
-    int k = pick_div(w.x, a.q);
-    if (k < 0) k = 0;
-    uint32_t v = a.sigma[i] + (uint32_t)k;
-    v = v >= a.q ? v - a.q : v;
-    a.sigma[i] = (uint8_t)v;
-}
-
-// Flattening in place: each lane stores only its own entry, and finds here
-// never write (a halving store by another lane could otherwise overwrite an
-// entry already flattened with an ancestor short of the root); concurrent
-// readers see either the old parent or the root, both on the path.
-__global__ __launch_bounds__(kBlock) void sw3_labels_kernel(Lat3 a)
-{
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= 6 * a.N) return;
-    uint32_t x = i, p = a.par[x];
-    while (p != x) {
-        x = p;
-        p = a.par[x];
-    }
-    a.par[i] = x;
-}
-
-// After the flip: the counters become the recount's (slots of the eta move's
-// N_HB_raw change are discarded; accepted-eta counts stay).
-__global__ void sw3_finish_kernel(Lat3 a)
-{
-    __shared__ int64_t part[2][kBlock / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int64_t v[2] = {a.rc[threadIdx.x], a.rc[kSlots + threadIdx.x]};
-    a.slots[threadIdx.x] = 0;
-    a.slots[kSlots + threadIdx.x] = 0;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        int64_t sm = v[k];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sm += __shfl_xor(sm, o, 64);
-        if (lane == 0) part[k][wv] = sm;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t h = 0, c = 0;
-        for (int i = 0; i < kBlock / 64; ++i) {
-            h += part[0][i];
-            c += part[1][i];
-        }
-        a.st->n_hb_raw = h;
-        a.st->n_coop = c;
-    }
-}
+#include "sw3_step.h"
 
 // ---------------------------------------------------------------------------
 // Full recount of the configuration (observables): N_HB_raw (eta = 1 edges
@@ -1238,6 +950,24 @@ size_t ws3_bytes(const cvf_params* p, int algo_mask)
     }
     return b;
 }
+
+// Tiles of a cluster update: 8 x 8 x 4 cells, one per thread, where the chip
+// has wavefronts to spare and the latency of a workgroup decides (a step takes
+// 44 / 56 / 76 / 97 us at L = 40 / 64 / 80 / 96 and 205 K); 16 x 8 x 8 cells,
+// four per thread, from L = 80 (54 / 61 / 76 / 91 us), with fewer face indices
+// and wider loads.
+using Sw3Big = Tile3<16, 8, 8, 4>;
+using Sw3Small = Tile3<8, 8, 4, 1>;
+bool sw3_big(uint64_t L) { return L >= 80; }
+
+// Plus nodes of the tiling (as many minus nodes): a face layer of L^2 per tile
+// along each axis.
+template <class TL>
+constexpr size_t tile_nodes(uint64_t L)
+{
+    return (size_t)(((L + TL::TX - 1) / TL::TX + (L + TL::TY - 1) / TL::TY + (L + TL::TZ - 1) / TL::TZ) * L * L);
+}
+size_t sw3_nodes(uint64_t L) { return sw3_big(L) ? tile_nodes<Sw3Big>(L) : tile_nodes<Sw3Small>(L); }
 
 // r3(m): integer points on the sphere i^2 + j^2 + k^2 = m, counted as
 // octant points with signs (each nonzero coordinate doubles the count).
@@ -1355,28 +1085,6 @@ DispatchEvents t_events(cvf3_state* st, int kind)
     return ev;
 }
 
-// Events on the stream around several launches (their interval includes
-// the gaps between them).
-void t_begin(cvf3_state* st, int kind, hipStream_t s)
-{
-    if (!st->timing) return;
-    hipEvent_t e0, e1;
-    if (hipEventCreate(&e0) != hipSuccess) return;
-    if (hipEventCreate(&e1) != hipSuccess) {
-        (void)hipEventDestroy(e0);
-        return;
-    }
-    (void)hipEventRecord(e0, s);
-    st->ev[kind].push_back(e0);
-    st->ev[kind].push_back(e1);
-}
-
-void t_end(cvf3_state* st, int kind, hipStream_t s)
-{
-    if (!st->timing || st->ev[kind].empty()) return;
-    (void)hipEventRecord(st->ev[kind].back(), s);
-}
-
 int drain3(cvf3_state* st)
 {
     int rc = CVF_OK;
@@ -1393,6 +1101,33 @@ int drain3(cvf3_state* st)
         v.clear();
     }
     return rc;
+}
+
+template <class TL>
+unsigned sw3_tiles(uint32_t L)
+{
+    return ((L + TL::TX - 1) / TL::TX) * ((L + TL::TY - 1) / TL::TY) * ((L + TL::TZ - 1) / TL::TZ);
+}
+
+template <class TL>
+TileGrid3 sw3_grid(uint32_t L)
+{
+    const uint32_t nx = (L + TL::TX - 1) / TL::TX, ny = (L + TL::TY - 1) / TL::TY;
+    return {nx, ny, 1.0f / (float)nx, 1.0f / (float)ny};
+}
+
+// The three launches of a cluster update over tiles TL.
+template <class TL>
+hipError_t sw3_update(cvf3_state* st, const Lat3& a, hipStream_t s)
+{
+    const TileGrid3 tg = sw3_grid<TL>(a.L);
+    const dim3 tiles(sw3_tiles<TL>(a.L));
+    hipError_t e = go(sw3_tile_kernel<TL>, tiles, dim3(TL::TT), s, t_events(st, CVF3_K_SW_BONDS), a, tg);
+    if (e == hipSuccess)
+        e = go(sw3_union_kernel, dim3(blocks_for(tile_nodes<TL>(a.L))), dim3(kBlock), s,
+               t_events(st, CVF3_K_SW_UNION), a, tg.nx, tg.ny, (a.L + TL::TZ - 1) / TL::TZ);
+    if (e == hipSuccess) e = go(sw3_flip_kernel<TL>, tiles, dim3(TL::TT), s, t_events(st, CVF3_K_SW_FLIP), a, tg);
+    return e;
 }
 
 }  // namespace
@@ -1460,13 +1195,16 @@ int cvf3_init(const cvf_params* p, int algo_mask, uint8_t* d_sigma, uint8_t* d_e
     a.tab = st->dtab;
     w += al256(sizeof(Tab3));
     st->sw = (algo_mask & CVF_ALGO_SW) != 0;
-    a.mask = nullptr;
     a.par = nullptr;
+    a.key = nullptr;
+    a.lroot = nullptr;
+    a.edge = nullptr;
     if (st->sw) {
-        const size_t N = (size_t)p->L * p->L * p->L;
-        a.mask = (uint32_t*)w;
-        w += al256(N * sizeof(uint32_t));
+        const size_t N = (size_t)p->L * p->L * p->L, F = sw3_nodes((uint64_t)p->L);
         a.par = (uint32_t*)w;
+        a.key = a.par + 2 * F;
+        a.lroot = (uint16_t*)(a.key + 2 * F);
+        a.edge = (uint8_t*)(a.lroot + 6 * N);
     }
     a.L = (uint32_t)p->L;
     a.N = a.L * a.L * a.L;
@@ -1485,6 +1223,7 @@ int cvf3_init(const cvf_params* p, int algo_mask, uint8_t* d_sigma, uint8_t* d_e
     a.dv_max = p->dv_max;
     a.do_volume = (p->flags & CVF_NO_VOLUME_MOVE) ? 0 : 1;
     a.quad = (a.L % 4 == 0) ? 1u : 0u;
+    a.eta_hb = 1;
     hipStream_t s = (hipStream_t)stream;
     rc = hs(hipMemcpyAsync(st->dtab, &st->htab, sizeof(Tab3), hipMemcpyHostToDevice, s));
     if (rc == CVF_OK) {
@@ -1560,34 +1299,14 @@ int cvf3_sw_steps(cvf3_state* st, int64_t nsteps, void* stream)
     if (!st || nsteps < 0) return CVF_EINVAL;
     if (!st->sw) return CVF_ESTATE;
     hipStream_t s = (hipStream_t)stream;
-    const Lat3& a = st->la;
+    Lat3 a = st->la;
+    a.eta_hb = 0;                                          // the flip recounts N_HB_raw
     for (int64_t i = 0; i < nsteps; ++i) {
         if (go(vol3_kernel, dim3(1), dim3(64), s, t_events(st, CVF3_K_VOLUME), a, kVolSw) != hipSuccess)
             return CVF_EHIP;
         if (eta_step(st, a, s) != hipSuccess) return CVF_EHIP;
-        if (go(sw3_bonds_kernel, dim3(blocks_for(a.N)), dim3(kBlock), s, t_events(st, CVF3_K_SW_BONDS), a) !=
-            hipSuccess)
-            return CVF_EHIP;
-        t_begin(st, CVF3_K_SW_UNION, s);
-        // tile phase: 16 x 8 x 8 cells (a sixteenth of the x links and an
-        // eighth of the y and z links cross a face) or 8 x 8 x 4
-        if (a.L % 16 == 0) {
-            sw3_tile_union_kernel<16, 8, 8><<<a.N / 1024, 1024, 0, s>>>(a);
-            sw3_union_kernel<<<blocks_for(a.N), kBlock, 0, s>>>(a, 16, 8, 8);
-        } else if (a.L % 8 == 0) {
-            sw3_tile_union_kernel<8, 8, 4><<<a.N / 256, 256, 0, s>>>(a);
-            sw3_union_kernel<<<blocks_for(a.N), kBlock, 0, s>>>(a, 8, 8, 4);
-        } else {
-            sw3_union_kernel<<<blocks_for(a.N), kBlock, 0, s>>>(a, 0, 0, 0);
-        }
-        t_end(st, CVF3_K_SW_UNION, s);
-        t_begin(st, CVF3_K_SW_FLIP, s);
-        sw3_flip_kernel<<<blocks_for(6ull * a.N), kBlock, 0, s>>>(a);    // also clears the recount's accumulators
-        recount3_kernel<<<blocks_for(a.N), kBlock, 0, s>>>(a);
-        sw3_finish_kernel<<<1, kBlock, 0, s>>>(a);
-        t_end(st, CVF3_K_SW_FLIP, s);
-        const int rc = hs(hipGetLastError());
-        if (rc != CVF_OK) return rc;
+        const hipError_t e = sw3_big(a.L) ? sw3_update<Sw3Big>(st, a, s) : sw3_update<Sw3Small>(st, a, s);
+        if (e != hipSuccess) return CVF_EHIP;
         st->sw_done = true;
     }
     return CVF_OK;
@@ -1599,11 +1318,9 @@ int cvf3_labels(cvf3_state* st, uint32_t* d_out, void* stream)
     if (!st->sw || !st->sw_done) return CVF_ESTATE;
     hipStream_t s = (hipStream_t)stream;
     const Lat3& a = st->la;
-    sw3_labels_kernel<<<blocks_for(6ull * a.N), kBlock, 0, s>>>(a);
-    int rc = hs(hipGetLastError());
-    if (rc == CVF_OK)
-        rc = hs(hipMemcpyAsync(d_out, a.par, 6ull * a.N * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    return rc;
+    if (sw3_big(a.L)) sw3_labels_kernel<Sw3Big><<<sw3_tiles<Sw3Big>(a.L), Sw3Big::T, 0, s>>>(a, sw3_grid<Sw3Big>(a.L), d_out);
+    else sw3_labels_kernel<Sw3Small><<<sw3_tiles<Sw3Small>(a.L), Sw3Small::T, 0, s>>>(a, sw3_grid<Sw3Small>(a.L), d_out);
+    return hs(hipGetLastError());
 }
 
 int cvf3_state_counts(cvf3_state* st, int64_t* d_counts, void* stream)

@@ -194,6 +194,16 @@ def test_cvf3_sw_tiled_cold(c3, oracle_mod, L):
     run3_mixed(c3, oracle_mod, op, [("sw", 1), ("sw", 3), ("met", 1), ("sw", 1)])
 
 
+@pytest.mark.parametrize("L", [14, 34, 36, 78, 80, 82, 88])
+def test_cvf3_sw_tile_edges(c3, oracle_mod, L):
+    """Lattices whose last tiles are ragged along every axis (8 x 8 x 4 cells
+    up to L = 78, 16 x 8 x 8 from L = 80), with L % 4 == 0 (dword cells) and
+    L % 4 == 2 (half words): cluster labels, sigma and every counter bit for
+    bit, also across a Metropolis step in between."""
+    op = oracle_mod.params_from_si(205.0, 0.1, L=L, seed=970 + L, v_init=1.1)
+    run3_mixed(c3, oracle_mod, op, [("sw", 2), ("met", 1), ("sw", 1)])
+
+
 @pytest.mark.parametrize("q", [2, 3, 5])
 def test_cvf3_sw_reduced_q_mixed(c3, oracle_mod, q):
     op = oracle_mod.params_from_si(240.0, 25.0, L=12, q=q, seed=950 + q)
