@@ -164,7 +164,7 @@ def bench_autocorr(torch, cvf, L=256, points=((270.0, 7), (300.0, 9))):
 
 
 ALU_OPS_3D = 39      # half a Philox block (20) + decision over five other arms (18) + eta gate (1)
-BYTES_3D = 9         # six own bond indices + facing one + the edge's eta read, one written
+BYTES_3D = 9         # a pass by itself: six own bond indices + facing one + the edge's eta read, one written
 
 
 def bench_cvf3(torch, W, K, L=260, with_autocorr=True):
@@ -187,14 +187,14 @@ def bench_cvf3(torch, W, K, L=260, with_autocorr=True):
     o = ch.obs()
     assert o["consistent"] == 1 and o["n_eta0"] == N
     ch.close()
-    pass_s = kt[cvf3.CVF3_K_PASS][1] * 1e-3
+    pass_s = kt[cvf3.CVF3_K_PASS][1] * kt[cvf3.CVF3_K_PASS][0] / (6 * K) * 1e-3      # a step's launches over its six passes
     gbs = N * BYTES_3D / pass_s / 1e9
     tops = N * ALU_OPS_3D / pass_s / 1e12
     return {"L": L, "N": N, "steps": K, "ms_per_step": round(t / K * 1e3, 4),
             "updates_per_ns": round(6 * N * K / t / 1e9, 2),
             "kernel_mean_us": {"volume": round(kt[cvf3.CVF3_K_VOLUME][1] * 1e3, 2),
                                "eta": round(kt[cvf3.CVF3_K_ETA][1] * 1e3, 2),
-                               "pass": round(kt[cvf3.CVF3_K_PASS][1] * 1e3, 2)},
+                               "pass": round(pass_s * 1e6, 2)},
             "pass_roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": round(gbs / HBM_PEAK_GBS, 4), "alg_bytes_per_update": BYTES_3D,
                               "alu": {"achieved": round(tops, 2), "peak": round(VALU_PEAK_TOPS, 2),

@@ -131,7 +131,8 @@ int cvf3_observables(cvf3_state *st, cvf3_obs *out, void *stream);
  * its start/stop events on its own dispatch (the kernel's execution alone). */
 #define CVF3_K_VOLUME 0     /* counter fold + volume move + pass order */
 #define CVF3_K_ETA    1     /* eta move over the checkerboard cubes    */
-#define CVF3_K_PASS   2     /* one arm-domain sigma pass               */
+#define CVF3_K_PASS   2     /* arm-domain sigma passes: four launches
+                               per step, of up to three passes each    */
 #define CVF3_K_SW_BONDS 3   /* SW links and components inside a tile   */
 #define CVF3_K_SW_UNION 4   /* SW union-find over tile-crossing links  */
 #define CVF3_K_SW_FLIP  5   /* SW cluster shift + recount              */

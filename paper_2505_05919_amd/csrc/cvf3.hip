@@ -8,10 +8,9 @@
 //   eta3_kernel   one thread per checkerboard cube: Metropolis move of the
 //                 cube's eta configuration (one of the nine perfect matchings
 //                 of the cube graph marks the eta = 0 edges)
-//   pass3_kernel  x6, one per arm in the drawn order: every cell's bond index
-//                 of that arm moves once (the arm-domain partition of
-//                 Sec. II.C); a lane moves two x-adjacent cells, which share
-//                 one Philox block
+//   pass3_kernel  x4: the six arm passes in the drawn order (the arm-domain
+//                 partition of Sec. II.C), grouped so that no two passes of a
+//                 launch are opposite arms
 // A Swendsen-Wang step (Sec. II.D) replaces the passes by sw3_tile_kernel
 // (links, components inside a tile), sw3_union_kernel (tile-crossing links,
 // global union-find over the tiles' face indices) and sw3_flip_kernel (cluster
@@ -20,6 +19,7 @@
 // c = x + L*(y + L*z); arms 0:+x 1:-x 2:+y 3:-y 4:+z 5:-z.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -39,14 +39,14 @@ constexpr int kSlots = 256;              // counter slots, spread to avoid one h
 constexpr int kAcc = 4;                  // d N_HB_raw, d N_sigma, sigma accepted, eta accepted
 constexpr int kRc = 10;                  // recount: N_HB_raw, N_sigma, N_q' (6), eta = 0 edges, spare
 constexpr int kBlock = 256;
-constexpr uint32_t kQuadsPerLane = 4;    // quad pass: quads per lane (grid-stride)
 
 struct Dev3State {
     double  v, u;
     int64_t t_next, t_cur;
     int64_t n_hb_raw, n_coop;
     int64_t met_att, met_acc, eta_att, eta_acc, vol_att, vol_acc;
-    int32_t theta, pad0;
+    int32_t theta;
+    uint32_t group_end;       // byte g: passes of the step's order up to the end of pass group g
     int32_t order[6];
     int32_t pad[2];
 };
@@ -141,17 +141,6 @@ __device__ __forceinline__ int pick_div(uint32_t w, uint32_t k)
     return (int)(w / d);
 }
 
-// The exact-block draw of {0..q-2} from one word, in closed form: with
-// d = floor(2^32/(q-1)), (q-1) d = 2^32 when q-1 is a power of two (never
-// NONE, k = floor(w (q-1) / 2^32)) and 2^32 - 1 when q-1 is 3 or 5 (NONE only
-// for w = 2^32 - 1, k = floor((w+1)(q-1) / 2^32)).  Returns false for NONE.
-__device__ __forceinline__ bool pick_other(uint32_t w, uint32_t qm1, bool odd, uint32_t& k)
-{
-    if (odd && w == 0xFFFFFFFFu) return false;
-    k = __umulhi(odd ? w + 1 : w, qm1);
-    return true;
-}
-
 // Corner vtx (bit 0: +x, 1: +y, 2: +z) of cube k: parity k / h^3 sets the
 // lowest corner (2i+par, 2j+par, 2l+par).
 struct Cube {
@@ -235,6 +224,7 @@ __global__ void state3_init_kernel(Lat3 a, double v_init)
         s->u = lj3(v_init, a.tab->r3);
         s->theta = v_init < 2.0 ? 1 : 0;
         for (int i = 0; i < 6; ++i) s->order[i] = i;
+        s->group_end = 0x06060606u;
     }
 }
 
@@ -356,7 +346,17 @@ __global__ __launch_bounds__(64) void vol3_kernel(Lat3 a, int mode)
         ord[i] = ord[i + k];
         ord[i + k] = tmp;
     }
-    for (int i = 0; i < 6; ++i) s->order[i] = ord[i];
+    // groups of consecutive passes without opposite arms (at most four)
+    uint32_t ends = 0x06060606u, seen = 0, g = 0;
+    for (uint32_t i = 0; i < 6; ++i) {
+        s->order[i] = ord[i];
+        if ((seen >> (ord[i] ^ 1)) & 1u) {
+            ends ^= (6u ^ i) << (8 * g++);
+            seen = 0;
+        }
+        seen |= 1u << ord[i];
+    }
+    s->group_end = ends;
     s->t_cur = t;
     s->t_next = t_next + 1;
     if (mode == kVolMet) {
@@ -566,283 +566,13 @@ __global__ __launch_bounds__(kBlock) void eta3_pair_kernel(Lat3 a)
     }
 }
 
-// ---------------------------------------------------------------------------
-// Arm-domain pass (Sec. II.C): arm A of every cell.  Lane = cell pair
-// (2p, 2p+1) of one x-row, Philox(p, t, A, DOM) words 0, 1 for the even cell
-// and 2, 3 for the odd one.  Own bond indices and the aligned facing/eta
-// pairs are 16-bit loads; the x arms' facing and eta pairs straddle the pair
-// and wrap at the row end, so they are byte loads.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void move_one(const uint32_t* met, int q, int theta, uint32_t own[6],
-                                         int A, uint32_t facing, uint32_t eta, uint32_t prop, uint32_t accw,
-                                         int& dhb, int& dco, int& nacc)
-{
-    const uint32_t qm1 = (uint32_t)q - 1;
-    uint32_t k;
-    if (!pick_other(prop, qm1, (qm1 & 1) && qm1 > 1, k)) return;      // NONE
-    const uint32_t old = own[A];
-    uint32_t neu = old + 1 + (uint32_t)k;
-    neu = neu >= (uint32_t)q ? neu - (uint32_t)q : neu;
-    const int dh = (int)(neu == facing) - (int)(old == facing);
-    int dc = 0;
-#pragma unroll
-    for (int b = 0; b < 6; ++b)
-        if (b != A) dc += (int)(neu == own[b]) - (int)(old == own[b]);
-    const int th = (theta && eta) ? 1 : 0;
-    const uint32_t thr = met[th * 33 + (dh + 1) * 11 + dc + 5];
-    if (thr == 0xFFFFFFFFu || accw < thr) {
-        own[A] = neu;
-        dhb += (int)eta * dh;
-        dco += dc;
-        nacc += 1;
-    }
-}
-
-template <int A>
-__device__ __forceinline__ void pass_pair(const Lat3& a, const uint32_t* met, uint32_t p,
-                                          uint32_t t, int theta, int (&cnt)[3])
-{
-    const uint32_t L = a.L, N = a.N;
-    const uint32_t c0 = 2 * p;
-    uint32_t own0[6], own1[6];
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        const uint32_t v = *(const uint16_t*)(a.sigma + (size_t)b * N + c0);
-        own0[b] = v & 0xFFu;
-        own1[b] = v >> 8;
-    }
-    uint32_t f0, f1, e0, e1, o = 0;
-    if (A == 0 || A == 1) {
-        const uint32_t yz = udiv(c0, L, a.invL);
-        const uint32_t x0 = c0 - yz * L;
-        if (A == 0) {                                     // facing: arm 1 of x0+1, x0+2
-            const uint32_t r2 = x0 + 2 == L ? c0 + 2 - L : c0 + 2;
-            f0 = a.sigma[(size_t)N + c0 + 1];
-            f1 = a.sigma[(size_t)N + r2];
-            const uint32_t ee = *(const uint16_t*)(a.eta + c0);
-            e0 = ee & 0xFFu;
-            e1 = ee >> 8;
-        } else {                                          // facing: arm 0 of x0-1, x0
-            const uint32_t l1 = x0 == 0 ? c0 + L - 1 : c0 - 1;
-            f0 = a.sigma[l1];
-            f1 = a.sigma[c0];
-            e0 = a.eta[l1];
-            e1 = a.eta[c0];
-        }
-    } else {
-        const uint32_t L2 = L * L;
-        if (A == 2 || A == 3) {
-            const uint32_t yz = udiv(c0, L, a.invL);
-            const uint32_t z = udiv(yz, L, a.invL);
-            const uint32_t y = yz - z * L;
-            if (A == 2) o = y == L - 1 ? c0 + L - L2 : c0 + L;
-            else o = y == 0 ? c0 + L2 - L : c0 - L;
-        } else if (A == 4) {
-            o = c0 + L2 >= N ? c0 + L2 - N : c0 + L2;
-        } else {
-            o = c0 >= L2 ? c0 - L2 : c0 + N - L2;
-        }
-        const uint32_t ff = *(const uint16_t*)(a.sigma + (size_t)(A ^ 1) * N + o);
-        f0 = ff & 0xFFu;
-        f1 = ff >> 8;
-        const uint32_t ee = *(const uint16_t*)(a.eta + (size_t)(A >> 1) * N + ((A & 1) ? o : c0));
-        e0 = ee & 0xFFu;
-        e1 = ee >> 8;
-    }
-    const uint4 w = philox(p, t, (uint32_t)A, kDom, a.key0, a.key1);
-    const uint32_t old0 = own0[A], old1 = own1[A];
-    move_one(met, (int)a.q, theta, own0, A, f0, e0, w.x, w.y, cnt[0], cnt[1], cnt[2]);
-    move_one(met, (int)a.q, theta, own1, A, f1, e1, w.z, w.w, cnt[0], cnt[1], cnt[2]);
-    if (own0[A] != old0 || own1[A] != old1)
-        *(uint16_t*)(a.sigma + (size_t)A * N + c0) = (uint16_t)(own0[A] | (own1[A] << 8));
-}
-
 // 0x01 in every byte of x that is zero, 0x00 elsewhere (no carry crosses a byte).
 __device__ __forceinline__ uint32_t zero_bytes(uint32_t x)
 {
     return (~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu)) >> 7;
 }
 
-// Sum of the four bytes of x (each small enough that no partial sum reaches 256).
-__device__ __forceinline__ uint32_t byte_sum(uint32_t x) { return (x * 0x01010101u) >> 24; }
-
-// Four cells per lane (L % 4 == 0): cells 4u..4u+3 of one x-row use the
-// Philox blocks of pairs 2u and 2u+1; own, facing and eta words are 32-bit
-// loads, the x arms' facing and eta words borrow one byte from the next or
-// previous word (wrapping at the row end).  The four moves are decided
-// together on packed bytes: the same proposals, table index and acceptance
-// as move_one, cell by cell.
-// Raw buffer over one plane (N bytes < 2^31): 32-bit lane offsets, base in SGPRs.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(uint8_t* base, uint32_t n)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)n, 0x00020000);
-}
-
-__device__ __forceinline__ uint32_t bld32(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t bld8(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return __builtin_amdgcn_raw_buffer_load_b8(r, (int)off, 0, 0);
-}
-
-template <int A>
-__device__ __forceinline__ void pass_quad(const Lat3& a, const uint32_t* met, uint32_t u, uint32_t t, int theta,
-                                          int (&cnt)[3])
-{
-    const uint32_t L = a.L, N = a.N;
-    const uint32_t c0 = 4 * u;
-    uint32_t ow[6];
-#pragma unroll
-    for (int b = 0; b < 6; ++b) ow[b] = bld32(plane_rsrc(a.sigma + (size_t)b * N, N), c0);
-    uint32_t fw, ew;
-    if (A == 0 || A == 1) {
-        const uint32_t yz = udiv(c0, L, a.invL);
-        const uint32_t x0 = c0 - yz * L;
-        const __amdgpu_buffer_rsrc_t e0 = plane_rsrc(a.eta, N);
-        if (A == 0) {                                     // arm 1 of x0+1 .. x0+4
-            const uint32_t nx = x0 + 4 == L ? c0 + 4 - L : c0 + 4;
-            const __amdgpu_buffer_rsrc_t s1 = plane_rsrc(a.sigma + (size_t)N, N);
-            fw = __builtin_amdgcn_alignbyte(bld8(s1, nx), ow[1], 1);
-            ew = bld32(e0, c0);
-        } else {                                          // arm 0 of x0-1 .. x0+2
-            const uint32_t px = x0 == 0 ? c0 + L - 1 : c0 - 1;
-            const __amdgpu_buffer_rsrc_t s0 = plane_rsrc(a.sigma, N);
-            fw = (ow[0] << 8) | bld8(s0, px);
-            ew = (bld32(e0, c0) << 8) | bld8(e0, px);
-        }
-    } else {
-        const uint32_t L2 = L * L;
-        uint32_t o;
-        if (A == 2 || A == 3) {
-            const uint32_t yz = udiv(c0, L, a.invL);
-            const uint32_t z = udiv(yz, L, a.invL);
-            const uint32_t y = yz - z * L;
-            if (A == 2) o = y == L - 1 ? c0 + L - L2 : c0 + L;
-            else o = y == 0 ? c0 + L2 - L : c0 - L;
-        } else if (A == 4) {
-            o = c0 + L2 >= N ? c0 + L2 - N : c0 + L2;
-        } else {
-            o = c0 >= L2 ? c0 - L2 : c0 + N - L2;
-        }
-        fw = bld32(plane_rsrc(a.sigma + (size_t)(A ^ 1) * N, N), o);
-        ew = bld32(plane_rsrc(a.eta + (size_t)(A >> 1) * N, N), (A & 1) ? o : c0);
-    }
-    const uint4 w0 = philox(2 * u, t, (uint32_t)A, kDom, a.key0, a.key1);
-    const uint4 w1 = philox(2 * u + 1, t, (uint32_t)A, kDom, a.key0, a.key1);
-    const uint32_t prop[4] = {w0.x, w0.z, w1.x, w1.z}, accw[4] = {w0.y, w0.w, w1.y, w1.w};
-    // proposals of the four cells, one byte each (a NONE draw keeps the old state)
-    const uint32_t q = a.q, qm1 = q - 1, oldw = ow[A];
-    const bool odd = (qm1 & 1) && qm1 > 1;
-    uint32_t nw = 0, valid = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t old = (oldw >> (8 * j)) & 0xFFu;
-        uint32_t k = 0;
-        const bool ok = pick_other(prop[j], qm1, odd, k);
-        uint32_t neu = old + 1 + k;
-        neu = neu >= q ? neu - q : neu;
-        neu = ok ? neu : old;
-        valid |= ok ? (0xFFu << (8 * j)) : 0u;
-        nw |= neu << (8 * j);
-    }
-    // equal-byte counts for all four cells at once: cn / co = other arms equal
-    // to the new / old state, hn / ho = facing arm equal to the new / old state
-    uint32_t cn = 0, co = 0;
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        if (b == A) continue;
-        cn += zero_bytes(nw ^ ow[b]);
-        co += zero_bytes(oldw ^ ow[b]);
-    }
-    const uint32_t hn = zero_bytes(nw ^ fw), ho = zero_bytes(oldw ^ fw);
-    const uint32_t thw = theta ? (ew & 0x01010101u) : 0u;
-    // table index th*33 + (dh+1)*11 + dc+5 per byte; every byte of the first
-    // term is >= 16 >= every byte of the second, so no borrow crosses bytes
-    const uint32_t idxw = (11u * hn + cn + 0x10101010u + 33u * thw) - (11u * ho + co);
-    uint32_t accm = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t thr = met[(idxw >> (8 * j)) & 0xFFu];
-        const bool acc = thr == 0xFFFFFFFFu || accw[j] < thr;
-        accm |= acc ? (0xFFu << (8 * j)) : 0u;
-    }
-    accm &= valid;
-    const uint32_t out = (nw & accm) | (oldw & ~accm);
-    const uint32_t em = accm & (ew * 0xFFu);            // accepted cells whose edge has eta = 1
-    cnt[0] += (int)byte_sum(hn & em) - (int)byte_sum(ho & em);
-    cnt[1] += (int)byte_sum(cn & accm) - (int)byte_sum(co & accm);
-    cnt[2] += __popc(accm) >> 3;
-    if (out != oldw) __builtin_amdgcn_raw_buffer_store_b32(out, plane_rsrc(a.sigma + (size_t)A * N, N), (int)c0, 0, 0);
-}
-
-__global__ __launch_bounds__(kBlock) void pass3_kernel(Lat3 a)
-{
-    __shared__ uint32_t met[66];
-    if (threadIdx.x < 66) met[threadIdx.x] = (&a.tab->met[0][0][0])[threadIdx.x];
-    const int arm = a.st->order[a.pass];
-    const uint32_t t = (uint32_t)a.st->t_cur;
-    const int theta = a.st->theta;
-    __syncthreads();
-    const uint32_t p = blockIdx.x * kBlock + threadIdx.x;
-    int cnt[3] = {0, 0, 0};
-    if (a.quad) {
-        // grid-stride over the quads: kQuadsPerLane per lane spreads the
-        // lane's fixed work (table load, counter reduction) over more moves
-        const uint32_t nq = a.N / 4, stride = gridDim.x * kBlock;
-#define CVF3_QUADS(ARM) for (uint32_t u = p; u < nq; u += stride) pass_quad<ARM>(a, met, u, t, theta, cnt)
-        switch (arm) {
-        case 0: CVF3_QUADS(0); break;
-        case 1: CVF3_QUADS(1); break;
-        case 2: CVF3_QUADS(2); break;
-        case 3: CVF3_QUADS(3); break;
-        case 4: CVF3_QUADS(4); break;
-        default: CVF3_QUADS(5); break;
-        }
-#undef CVF3_QUADS
-    } else if (p < a.N / 2) {
-        switch (arm) {
-        case 0: pass_pair<0>(a, met, p, t, theta, cnt); break;
-        case 1: pass_pair<1>(a, met, p, t, theta, cnt); break;
-        case 2: pass_pair<2>(a, met, p, t, theta, cnt); break;
-        case 3: pass_pair<3>(a, met, p, t, theta, cnt); break;
-        case 4: pass_pair<4>(a, met, p, t, theta, cnt); break;
-        default: pass_pair<5>(a, met, p, t, theta, cnt); break;
-        }
-    }
-    // The three counters of a lane (d N_HB_raw in [-16, 16], d N_sigma in
-    // [-80, 80], accepted in [0, 16] for four quads) biased and packed into
-    // one word and summed over 16 lanes (sums at most 512, 2560 and 256:
-    // fields of 10, 12 and 9 bits), then unpacked and summed over the four
-    // 16-lane rows.
-    static_assert(kQuadsPerLane <= 4, "field widths below hold for up to four quads per lane");
-    uint32_t v = (uint32_t)(cnt[1] + 80) | ((uint32_t)(cnt[0] + 16) << 12) | ((uint32_t)cnt[2] << 22);
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) v += (uint32_t)__shfl_xor((int)v, o, 64);
-    int r3[3] = {(int)((v >> 12) & 0x3FFu) - 16 * 16, (int)(v & 0xFFFu) - 16 * 80, (int)(v >> 22)};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        r3[k] += __shfl_xor(r3[k], 16, 64);
-        r3[k] += __shfl_xor(r3[k], 32, 64);
-    }
-    __shared__ int part[3][kBlock / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) {
-        part[0][wv] = r3[0];
-        part[1][wv] = r3[1];
-        part[2][wv] = r3[2];
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        int64_t sm = 0;
-        for (int i = 0; i < kBlock / 64; ++i) sm += part[threadIdx.x][i];
-        if (sm) atomicAdd((unsigned long long*)(a.slots + (size_t)threadIdx.x * kSlots + blockIdx.x % kSlots),
-                          (unsigned long long)sm);
-    }
-}
-
+#include "pass3.h"
 #include "sw3_step.h"
 
 // ---------------------------------------------------------------------------
@@ -931,6 +661,7 @@ struct cvf3_state {
     bool       timing;
     bool       sw;
     bool       sw_done;
+    bool       le;            // no Metropolis threshold is 0: acceptance is word <= threshold - 1
     std::vector<hipEvent_t> ev[CVF3_K_COUNT];
     int64_t    launches[CVF3_K_COUNT];
     double     total_ms[CVF3_K_COUNT];
@@ -1130,6 +861,46 @@ hipError_t sw3_update(cvf3_state* st, const Lat3& a, hipStream_t s)
     return e;
 }
 
+template <int Q, bool LE>
+hipError_t pass_launch_q(cvf3_state* st, const Lat3& a, unsigned grid, const PassShape& sh, hipStream_t s)
+{
+    const DispatchEvents ev = t_events(st, CVF3_K_PASS);
+    if (a.quad) return go(pass3_kernel<Q, LE, true>, dim3(grid), dim3(kBlock), s, ev, a, sh);
+    return go(pass3_kernel<Q, LE, false>, dim3(grid), dim3(kBlock), s, ev, a, sh);
+}
+
+template <int Q>
+hipError_t pass_launch_le(cvf3_state* st, const Lat3& a, unsigned grid, const PassShape& sh, hipStream_t s)
+{
+    return st->le ? pass_launch_q<Q, true>(st, a, grid, sh, s) : pass_launch_q<Q, false>(st, a, grid, sh, s);
+}
+
+// Pass group a.pass.  Up to four quads per lane spread a lane's fixed work
+// (table load, counter reduction) over more moves; smaller lattices take fewer,
+// so that the launch keeps the 2048 workgroups that fill the chip (at L = 130
+// a step takes 64 us this way, 76 us with at least 256 workgroups).
+hipError_t pass_launch(cvf3_state* st, const Lat3& a, hipStream_t s)
+{
+    PassShape sh;
+    sh.per_row = (a.L + 3) / 4;
+    sh.quads = sh.per_row * a.L * a.L;
+    sh.inv_row = 1.0 / (double)sh.per_row;
+    const uint32_t one = blocks_for(sh.quads);
+    const uint32_t per_lane = std::min(kMaxQuadsPerLane, std::max(1u, one / 2048u));
+    const uint32_t grid = (one + per_lane - 1) / per_lane, step = grid * kBlock;
+    const uint32_t rows = step / sh.per_row;
+    sh.sj = step % sh.per_row;
+    sh.sy = rows % a.L;
+    sh.sz = rows / a.L;
+    switch (a.q) {
+    case 2: return pass_launch_le<2>(st, a, grid, sh, s);
+    case 3: return pass_launch_le<3>(st, a, grid, sh, s);
+    case 4: return pass_launch_le<4>(st, a, grid, sh, s);
+    case 5: return pass_launch_le<5>(st, a, grid, sh, s);
+    default: return pass_launch_le<6>(st, a, grid, sh, s);
+    }
+}
+
 }  // namespace
 
 extern "C" {
@@ -1224,6 +995,9 @@ int cvf3_init(const cvf_params* p, int algo_mask, uint8_t* d_sigma, uint8_t* d_e
     a.do_volume = (p->flags & CVF_NO_VOLUME_MOVE) ? 0 : 1;
     a.quad = (a.L % 4 == 0) ? 1u : 0u;
     a.eta_hb = 1;
+    st->le = true;
+    for (int k = 0; k < 66; ++k)
+        if ((&st->htab.met[0][0][0])[k] == 0) st->le = false;
     hipStream_t s = (hipStream_t)stream;
     rc = hs(hipMemcpyAsync(st->dtab, &st->htab, sizeof(Tab3), hipMemcpyHostToDevice, s));
     if (rc == CVF_OK) {
@@ -1284,12 +1058,8 @@ int cvf3_steps(cvf3_state* st, int64_t nsteps, void* stream)
         if (go(vol3_kernel, dim3(1), dim3(64), s, t_events(st, CVF3_K_VOLUME), a, kVolMet) != hipSuccess)
             return CVF_EHIP;
         if (eta_step(st, a, s) != hipSuccess) return CVF_EHIP;
-        const unsigned grid = blocks_for(a.quad ? (a.N / 4 + kQuadsPerLane - 1) / kQuadsPerLane : a.N / 2);
-        for (uint32_t pass = 0; pass < 6; ++pass) {
-            a.pass = pass;
-            if (go(pass3_kernel, dim3(grid), dim3(kBlock), s, t_events(st, CVF3_K_PASS), a) != hipSuccess)
-                return CVF_EHIP;
-        }
+        for (a.pass = 0; a.pass < 4; ++a.pass)
+            if (pass_launch(st, a, s) != hipSuccess) return CVF_EHIP;
     }
     return CVF_OK;
 }

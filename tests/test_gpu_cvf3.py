@@ -109,6 +109,16 @@ def test_cvf3_paper_size(c3, oracle_mod):
     run3(c3, oracle_mod, op, [1])
 
 
+@pytest.mark.parametrize("L,q,n", [(4, 6, 40), (6, 5, 40), (12, 2, 30), (14, 3, 20), (14, 6, 20), (20, 4, 20),
+                                   (66, 6, 3), (166, 6, 1), (258, 5, 1)])
+def test_cvf3_pass_groups(c3, oracle_mod, L, q, n):
+    """The arm passes in their groups, over enough steps that every shape of
+    the drawn order (two to four groups) occurs: full and two-cell quads, one
+    to four quads per lane, every q."""
+    op = oracle_mod.params_from_si(230.0, 0.1, L=L, q=q, seed=640 + L + q)
+    run3(c3, oracle_mod, op, [1, n] if n > 1 else [1])
+
+
 @pytest.mark.parametrize("L", [1288, 1290])
 def test_cvf3_max_size(c3, oracle_mod, L):
     """The largest lattices (N = L^3 < 2^31; 1288 runs the quad pass and the
