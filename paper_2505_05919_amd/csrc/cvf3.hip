@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -38,6 +39,8 @@ constexpr uint32_t kInit = 0, kVol = 1, kSwb = 3, kSwf = 4, kOrd = 5, kDom = 6, 
 constexpr int kSlots = 256;              // counter slots, spread to avoid one hot atomic
 constexpr int kAcc = 4;                  // d N_HB_raw, d N_sigma, sigma accepted, eta accepted
 constexpr int kRc = 10;                  // recount: N_HB_raw, N_sigma, N_q' (6), eta = 0 edges, spare
+constexpr int kRcSpread = 16, kRcBlocks = 1024;
+constexpr int kRcState = kRc * kRcSpread;    // word of the recount area where a fold leaves a copy of the state
 constexpr int kBlock = 256;
 
 struct Dev3State {
@@ -50,6 +53,7 @@ struct Dev3State {
     int32_t order[6];
     int32_t pad[2];
 };
+static_assert(sizeof(Dev3State) % 8 == 0 && sizeof(Dev3State) <= 64 * 8, "copied as words, one per lane");
 
 struct Tab3 {
     uint32_t met[2][3][11];   // sigma move: [theta*eta][dh+1][dc+5]
@@ -65,7 +69,7 @@ struct Lat3 {
     uint8_t*   eta;
     Dev3State* st;
     int64_t*   slots;         // [kAcc][kSlots]
-    int64_t*   rc;            // [kRc][kSlots]
+    int64_t*   rc;            // recount sums [kRc][kRcSpread], then a copy of the state
     const Tab3* tab;          // device copy
     // Swendsen-Wang only (NULL without it); F plus nodes, see sw3_step.h
     uint32_t*  par;           // [2F] parents of the tile-face nodes
@@ -95,27 +99,6 @@ __device__ __forceinline__ int wave_sum(int v)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
-}
-
-// Sums K per-thread values over the workgroup and adds them to slot
-// (blockIdx % kSlots) of each of K counters (stride kSlots).
-template <int K>
-__device__ void block_slots(int (&v)[K], int64_t* dst)
-{
-    __shared__ int part[K][kBlock / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int s = wave_sum(v[k]);
-        if (lane == 0) part[k][w] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x < K) {
-        int64_t s = 0;
-        for (int i = 0; i < kBlock / 64; ++i) s += part[threadIdx.x][i];
-        if (s) atomicAdd((unsigned long long*)(dst + (size_t)threadIdx.x * kSlots + blockIdx.x % kSlots),
-                         (unsigned long long)s);
-    }
 }
 
 // U_LJ per molecule on the cubic lattice (Sec. II.A): shells m = |n|^2 in
@@ -235,7 +218,9 @@ constexpr int kVolMet = 0, kVolFold = 1, kVolSw = 2;
 // dH = N (u(v') - u(v)) + P N (v' - v) + (theta' - theta)(P v_HB - J) N_HB_raw
 // with words 0, 1 of Philox(0, t, 0, VOL); order: Fisher-Yates over 0..5
 // with words 0..3 of Philox(0, t, 0, ORD) and word 0 of Philox(0, t, 1, ORD).
-// mode 0: full step opening; mode 1: fold only.
+// mode 0: full step opening; mode 1: fold only (clears the recount's sums and
+// leaves a copy of the folded state behind them, so that one copy to the host
+// brings both).
 // ---------------------------------------------------------------------------
 // One wavefront: lanes fold the counter slots (kSlots / 64 each), lanes 0-2
 // draw the VOL block and the two ORD blocks at once, lanes 1..36 evaluate one
@@ -261,6 +246,8 @@ __global__ __launch_bounds__(64) void vol3_kernel(Lat3 a, int mode)
     const int64_t hb0 = s->n_hb_raw, co0 = s->n_coop, ma0 = s->met_acc, ea0 = s->eta_acc;
     const int64_t matt0 = s->met_att, eatt0 = s->eta_att, vatt0 = s->vol_att, vacc0 = s->vol_acc;
     const double r3 = (lane >= 1 && lane <= 36) ? a.tab->r3[lane] : 0.0;
+    constexpr int kWords = sizeof(Dev3State) / 8;
+    const int64_t word = lane < kWords ? ((const int64_t*)s)[lane] : 0;
     int64_t r[kAcc];
 #pragma unroll
     for (int k = 0; k < kAcc; ++k) {
@@ -300,8 +287,20 @@ __global__ __launch_bounds__(64) void vol3_kernel(Lat3 a, int mode)
         }
     }
     __syncthreads();
+    Dev3State* copy = (Dev3State*)(a.rc + kRcState);
+    if (mode == kVolFold) {
+        for (int i = lane; i < kRcState; i += 64) a.rc[i] = 0;
+        if (lane < kWords) ((int64_t*)copy)[lane] = word;
+        __builtin_amdgcn_s_waitcnt(0);                     // before lane 0 writes the folded counters into it
+    }
     if (lane != 0) return;
     const int64_t n_hb = hb0 + r[0];
+    if (mode == kVolFold) {
+        copy->n_hb_raw = n_hb;
+        copy->n_coop = co0 + r[1];
+        copy->met_acc = ma0 + r[2];
+        copy->eta_acc = ea0 + r[3];
+    }
     s->n_hb_raw = n_hb;
     s->n_coop = co0 + r[1];
     s->met_acc = ma0 + r[2];
@@ -579,37 +578,53 @@ __device__ __forceinline__ uint32_t zero_bytes(uint32_t x)
 // Full recount of the configuration (observables): N_HB_raw (eta = 1 edges
 // with equal facing sigma), N_sigma (15 pairs per cell), N_q', eta = 0 edges.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void recount3_kernel(Lat3 a)
+// Exact for any byte values.  At most kRcBlocks workgroups add their sums to
+// kRcSpread addresses per counter (with a workgroup per 256 cells and 256
+// addresses the recount took 176 us at 260^3, 32 us of which read the lattice).
+template <bool W>
+__global__ __launch_bounds__(kBlock) void recount3_kernel(Lat3 a, PassShape sh)
 {
-    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
     int v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    if (c < a.N) {
-        const uint32_t L = a.L, N = a.N, L2 = L * L;
-        const uint32_t yz = udiv(c, L, a.invL);
-        const uint32_t x = c - yz * L;
-        const uint32_t z = udiv(yz, L, a.invL);
-        const uint32_t y = yz - z * L;
-        uint32_t s[6];
+    const uint32_t L = a.L, N = a.N, L2 = L * L;
+    for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < sh.quads; u += gridDim.x * kBlock) {
+        const uint32_t yz = udiv(u, sh.per_row, sh.inv_row), z = udiv(yz, L, a.invL), y = yz - z * L;
+        const uint32_t x = 4 * (u - yz * sh.per_row), c = x + L * yz, n = W || x + 4 <= L ? 4u : 2u;
+        const uint32_t have = n == 4 ? 0x01010101u : 0x0101u;
+        uint32_t s[6], f[3];
 #pragma unroll
-        for (int b = 0; b < 6; ++b) s[b] = a.sigma[(size_t)b * N + c];
-        const uint32_t nbr[3] = {x == L - 1 ? c + 1 - L : c + 1, y == L - 1 ? c + L - L2 : c + L,
-                                 c + L2 >= N ? c + L2 - N : c + L2};
+        for (int b = 0; b < 6; ++b) s[b] = bld4<W>(plane_rsrc(a.sigma + (size_t)b * N, N), c, n);
+        const uint32_t nx = bld8(plane_rsrc(a.sigma + (size_t)N, N), x + n == L ? c + n - L : c + n);
+        f[0] = n == 4 ? (s[1] >> 8) | (nx << 24) : ((s[1] >> 8) & 0xFFu) | (nx << 8);
+        f[1] = bld4<W>(plane_rsrc(a.sigma + 3 * (size_t)N, N), y == L - 1 ? c + L - L2 : c + L, n);
+        f[2] = bld4<W>(plane_rsrc(a.sigma + 5 * (size_t)N, N), z == L - 1 ? c + L2 - N : c + L2, n);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            const uint32_t e = a.eta[(size_t)d * N + c];
-            v[0] += (e != 0 && s[2 * d] == a.sigma[(size_t)(2 * d + 1) * N + nbr[d]]) ? 1 : 0;
-            v[8] += e == 0 ? 1 : 0;
+            const uint32_t off = zero_bytes(bld4<W>(plane_rsrc(a.eta + (size_t)d * N, N), c, n));
+            v[0] += __popc(zero_bytes(s[2 * d] ^ f[d]) & ~off & have);
+            v[8] += __popc(off & have);
         }
 #pragma unroll
-        for (int i = 0; i < 6; ++i)
+        for (int i = 0; i < 6; ++i) {
 #pragma unroll
-            for (int j = i + 1; j < 6; ++j) v[1] += s[i] == s[j] ? 1 : 0;
+            for (int j = i + 1; j < 6; ++j) v[1] += __popc(zero_bytes(s[i] ^ s[j]) & have);
 #pragma unroll
-        for (int b = 0; b < 6; ++b)
-#pragma unroll
-            for (int k = 0; k < 6; ++k) v[2 + k] += s[b] == (uint32_t)k ? 1 : 0;
+            for (uint32_t k = 0; k < 6; ++k) v[2 + k] += __popc(zero_bytes(s[i] ^ (k * 0x01010101u)) & have);
+        }
     }
-    block_slots<9>(v, a.rc);
+    __shared__ int part[9][kBlock / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const int sm = wave_sum(v[k]);
+        if (lane == 0) part[k][w] = sm;
+    }
+    __syncthreads();
+    if (threadIdx.x < 9) {
+        int64_t sm = 0;
+        for (int i = 0; i < kBlock / 64; ++i) sm += part[threadIdx.x][i];
+        if (sm) atomicAdd((unsigned long long*)(a.rc + threadIdx.x * kRcSpread + blockIdx.x % kRcSpread),
+                          (unsigned long long)sm);
+    }
 }
 
 // N_q' of the current sigma added to out[0..5]: the 6N bytes read as 32-bit
@@ -637,11 +652,6 @@ __global__ __launch_bounds__(kBlock) void counts3_kernel(const uint32_t* __restr
         for (int i = 0; i < kBlock / 64; ++i) sm += part[threadIdx.x][i];
         if (sm) atomicAdd((unsigned long long*)(out + threadIdx.x), (unsigned long long)sm);
     }
-}
-
-__global__ void zero_kernel(int64_t* p, int n)
-{
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
 inline unsigned blocks_for(uint64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -861,6 +871,43 @@ hipError_t sw3_update(cvf3_state* st, const Lat3& a, hipStream_t s)
     return e;
 }
 
+PassShape quad_shape(const Lat3& a)
+{
+    PassShape sh = {};
+    sh.per_row = (a.L + 3) / 4;
+    sh.quads = sh.per_row * a.L * a.L;
+    sh.inv_row = 1.0 / (double)sh.per_row;
+    return sh;
+}
+
+// The recount's sums and the folded chain state, as the host reads them.
+struct Recount3 {
+    int64_t sums[kRc][kRcSpread];
+    Dev3State st;
+    int64_t total(int k) const
+    {
+        int64_t t = 0;
+        for (int i = 0; i < kRcSpread; ++i) t += sums[k][i];
+        return t;
+    }
+};
+static_assert(offsetof(Recount3, st) == kRcState * sizeof(int64_t), "one copy brings both");
+static_assert(sizeof(Recount3) <= kRc * kSlots * sizeof(int64_t), "fits the recount area");
+
+// Folds the counters, recounts the lattice and reads both (synchronises).
+int recount3(const Lat3& a, hipStream_t s, Recount3* out)
+{
+    vol3_kernel<<<1, 64, 0, s>>>(a, kVolFold);
+    const PassShape sh = quad_shape(a);
+    const unsigned grid = std::min((unsigned)kRcBlocks, blocks_for(sh.quads));
+    if (a.quad) recount3_kernel<true><<<grid, kBlock, 0, s>>>(a, sh);
+    else recount3_kernel<false><<<grid, kBlock, 0, s>>>(a, sh);
+    int rc = hs(hipGetLastError());
+    if (rc == CVF_OK) rc = hs(hipMemcpyAsync(out, a.rc, sizeof(Recount3), hipMemcpyDeviceToHost, s));
+    if (rc == CVF_OK) rc = hs(hipStreamSynchronize(s));
+    return rc;
+}
+
 template <int Q, bool LE>
 hipError_t pass_launch_q(cvf3_state* st, const Lat3& a, unsigned grid, const PassShape& sh, hipStream_t s)
 {
@@ -881,10 +928,7 @@ hipError_t pass_launch_le(cvf3_state* st, const Lat3& a, unsigned grid, const Pa
 // a step takes 64 us this way, 76 us with at least 256 workgroups).
 hipError_t pass_launch(cvf3_state* st, const Lat3& a, hipStream_t s)
 {
-    PassShape sh;
-    sh.per_row = (a.L + 3) / 4;
-    sh.quads = sh.per_row * a.L * a.L;
-    sh.inv_row = 1.0 / (double)sh.per_row;
+    PassShape sh = quad_shape(a);
     const uint32_t one = blocks_for(sh.quads);
     const uint32_t per_lane = std::min(kMaxQuadsPerLane, std::max(1u, one / 2048u));
     const uint32_t grid = (one + per_lane - 1) / per_lane, step = grid * kBlock;
@@ -1010,23 +1054,12 @@ int cvf3_init(const cvf_params* p, int algo_mask, uint8_t* d_sigma, uint8_t* d_e
         rc = hs(hipGetLastError());
     }
     if (rc == CVF_OK) {                              // initial counters from a recount
-        zero_kernel<<<1, kBlock, 0, s>>>(a.rc, kRc * kSlots);
-        recount3_kernel<<<blocks_for(a.N), kBlock, 0, s>>>(a);
-        rc = hs(hipGetLastError());
-    }
-    std::vector<int64_t> h((size_t)kRc * kSlots);
-    if (rc == CVF_OK) rc = hs(hipMemcpyAsync(h.data(), a.rc, h.size() * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    if (rc == CVF_OK) rc = hs(hipStreamSynchronize(s));
-    if (rc == CVF_OK) {
-        Dev3State ds;
-        rc = hs(hipMemcpy(&ds, a.st, sizeof(ds), hipMemcpyDeviceToHost));
+        Recount3 r;
+        rc = recount3(a, s, &r);
         if (rc == CVF_OK) {
-            ds.n_hb_raw = ds.n_coop = 0;
-            for (int i = 0; i < kSlots; ++i) {
-                ds.n_hb_raw += h[0 * kSlots + i];
-                ds.n_coop += h[1 * kSlots + i];
-            }
-            rc = hs(hipMemcpy(a.st, &ds, sizeof(ds), hipMemcpyHostToDevice));
+            r.st.n_hb_raw = r.total(0);
+            r.st.n_coop = r.total(1);
+            rc = hs(hipMemcpy(a.st, &r.st, sizeof(r.st), hipMemcpyHostToDevice));
         }
     }
     if (rc != CVF_OK) {
@@ -1109,19 +1142,12 @@ int cvf3_observables(cvf3_state* st, cvf3_obs* out, void* stream)
     if (!st || !out) return CVF_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     const Lat3& a = st->la;
-    vol3_kernel<<<1, 64, 0, s>>>(a, kVolFold);
-    zero_kernel<<<1, kBlock, 0, s>>>(a.rc, kRc * kSlots);
-    recount3_kernel<<<blocks_for(a.N), kBlock, 0, s>>>(a);
-    int rc = hs(hipGetLastError());
-    std::vector<int64_t> h((size_t)kRc * kSlots);
-    Dev3State ds;
-    if (rc == CVF_OK) rc = hs(hipMemcpyAsync(h.data(), a.rc, h.size() * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    if (rc == CVF_OK) rc = hs(hipMemcpyAsync(&ds, a.st, sizeof(ds), hipMemcpyDeviceToHost, s));
-    if (rc == CVF_OK) rc = hs(hipStreamSynchronize(s));
+    Recount3 r;
+    const int rc = recount3(a, s, &r);
     if (rc != CVF_OK) return rc;
-    int64_t tot[kRc] = {0};
-    for (int k = 0; k < kRc; ++k)
-        for (int i = 0; i < kSlots; ++i) tot[k] += h[(size_t)k * kSlots + i];
+    const Dev3State& ds = r.st;
+    int64_t tot[kRc];
+    for (int k = 0; k < kRc; ++k) tot[k] = r.total(k);
     memset(out, 0, sizeof(*out));
     const double Nd = a.Nd;
     out->step = ds.t_next;

@@ -275,7 +275,7 @@ hipError_t chain_start(cvf_state* st, bool tables_by_kernel, hipStream_t s)
     if (e == hipSuccess) e = launch_state_init(st->dst, st->slots, st->dtab, st->p.v_init, s);
     if (e == hipSuccess && !(st->p.flags & CVF_KEEP_SIGMA)) e = launch_sigma_init(st->la, s);
     if (e == hipSuccess && st->has_sw) e = launch_sw_counters_init(st->la, s);
-    if (e == hipSuccess) e = launch_recount(st->la, st->slots, kSlots, 0, 0, s);
+    if (e == hipSuccess) e = launch_recount(st->la, st->slots, s);
     return e;
 }
 
@@ -377,11 +377,8 @@ hipError_t observables_launch(cvf_state* st, hipStream_t s)
     VolArgs v = st->va;
     v.mode = kVolFold;
     hipError_t e = launch_volume(v, s);
-    if (e == hipSuccess) e = launch_obs_zero(st->dobs, s);
-    if (e == hipSuccess) e = launch_recount(st->la, st->dobs->acc, 1, 1, 0, s);
     if (e == hipSuccess)
-        e = launch_obs_final(st->dobs, st->dst, st->dtab, (double)st->N, st->p.J, st->p.Jsigma, st->p.P,
-                             st->p.vHB, s);
+        e = launch_obs(st->la, {st->dobs, (double)st->N, st->p.J, st->p.Jsigma, st->p.P, st->p.vHB}, s);
     return e;
 }
 

@@ -57,8 +57,11 @@ struct DevTables {
 };
 
 // Observable accumulators + the final record copied to the host.
+constexpr int kObsSpread = 4, kObsAcc = 8 * kObsSpread;
 struct DevObs {
-    int64_t acc[8];          // recount: n_hb_raw, n_coop, count[0..5]
+    int64_t acc[kObsAcc];    // recount: n_hb_raw, n_coop, count[0..5], kObsSpread addresses each
+    uint32_t arrived;        // workgroups of the recount that have added theirs
+    uint32_t pad;
     cvf_obs out;
 };
 
@@ -124,6 +127,12 @@ struct LatticeArgs {
     uint32_t met_le;         // 1: no Metropolis threshold is 0, so acceptance is one compare (word <= thr - 1)
 };
 
+// The observables of a chain: where they go, and the constants of Eq. (1), (3).
+struct ObsArgs {
+    DevObs* obs;
+    double Nd, J, Jsigma, P, vHB;
+};
+
 struct VolArgs {
     DevState* st;
     int64_t* slots;
@@ -170,14 +179,13 @@ hipError_t launch_volume(const VolArgs& a, hipStream_t s, DispatchEvents ev = {}
 hipError_t launch_met_colour(const LatticeArgs& a, int colour, hipStream_t s, DispatchEvents ev = {});
 // Arm-domain sweep: pass 0..3 of the step's drawn arm order (any L >= 2).
 hipError_t launch_met_domain(const LatticeArgs& a, uint32_t pass, hipStream_t s, DispatchEvents ev = {});
-// step_gate: the recount closes an SW step and is skipped with it.
-hipError_t launch_recount(const LatticeArgs& a, int64_t* out, int spread, int with_counts, int step_gate,
-                          hipStream_t s);
-hipError_t launch_obs_zero(DevObs* o, hipStream_t s);
+// N_HB_raw and N_sigma of the lattice added to the counter slots.
+hipError_t launch_recount(const LatticeArgs& a, int64_t* slots, hipStream_t s);
+// The recount with state counts and the observables record, after a volume
+// launch in fold mode (which clears the accumulators).
+hipError_t launch_obs(const LatticeArgs& a, const ObsArgs& o, hipStream_t s);
 // N_q' of the current sigma added to out[0..5] (sigma 4-byte aligned).
 hipError_t launch_state_counts(const LatticeArgs& a, int64_t* out, hipStream_t s);
-hipError_t launch_obs_final(DevObs* o, const DevState* st, const DevTables* tab, double Nd, double J,
-                            double Jsigma, double P, double vHB, hipStream_t s);
 // Tiled SW step: bonds + in-tile unions + the tile-crossing links (each
 // united by the later of its two tiles), then the cluster shift fused with
 // the recount.  Labels are written out on request.

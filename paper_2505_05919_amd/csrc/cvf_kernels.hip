@@ -186,6 +186,11 @@ __device__ void volume_step(const VolArgs& a, double* term, BatchEntry* out = nu
     const int64_t n_hb = hb0 + r[0];
     const int64_t n_co = co0 + r[1];
     const int64_t m_acc = macc0 + r[2];
+    if (a.mode == kVolFold) {                        // observables follow: clear their accumulators
+        DevObs* obs = (DevObs*)((char*)st - kOffState + kOffObs);
+        if (lane < kObsAcc) obs->acc[lane] = 0;
+        if (lane == 0) obs->arrived = 0;
+    }
     if (a.mode == kVolFold || t_next >= stop_at) {   // fold only; at the step limit the step kernels skip
         if (lane == 0) {
             st->n_hb_raw = n_hb;
@@ -271,18 +276,8 @@ __global__ __launch_bounds__(64) void volume_kernel(VolArgs a)
 #include "met_sweep.h"
 #include "met_domain.h"
 
-// Raw buffer helpers for the recount (the sweep kernels have their own).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(uint8_t* p, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, (int)bytes, 0x00020000);
-}
-
-__device__ __forceinline__ uint32_t ld8b(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-{
-    return __builtin_amdgcn_raw_buffer_load_b8(r, (int)voff, (int)soff, 0);
-}
-
 #include "sw_step.h"
+#include "recount.h"
 
 // N_q' of the current sigma (q' < 6), added to out[0..5].  The planes are
 // read as 32-bit words; the bytes of w equal to k are the zero bytes of
@@ -302,38 +297,6 @@ __global__ __launch_bounds__(kBlock) void state_counts_kernel(const uint32_t* __
         }
     }
     block_add<6>(c, out, 1);
-}
-
-__global__ void obs_zero_kernel(DevObs* o)
-{
-    if (threadIdx.x < 8) o->acc[threadIdx.x] = 0;
-}
-
-// Observables from the recount and the chain scalars (Eq. (1), (3)).
-__global__ void obs_final_kernel(DevObs* o, const DevState* st, const DevTables* tab, double Nd, double J,
-                                 double Jsigma, double P, double vHB)
-{
-    if (threadIdx.x != 0) return;
-    cvf_obs& r = o->out;
-    r.step = st->t_next;
-    r.n_hb_raw = o->acc[0];
-    r.n_hb = st->theta ? o->acc[0] : 0;
-    r.n_coop = o->acc[1];
-    int64_t mx = 0;
-    for (int k = 0; k < 6; ++k) {
-        r.count[k] = o->acc[2 + k];
-        mx = r.count[k] > mx ? r.count[k] : mx;
-    }
-    r.met_attempted = st->met_att;
-    r.met_accepted = st->met_acc;
-    r.vol_attempted = st->vol_att;
-    r.vol_accepted = st->vol_acc;
-    r.v = st->v;
-    r.V = (Nd * st->v) + (vHB * (double)r.n_hb);
-    r.H = (((Nd * lj_energy(st->v, tab->r2)) - (J * (double)r.n_hb)) - (Jsigma * (double)r.n_coop)) + (P * r.V);
-    r.M = (double)mx / (4.0 * Nd);
-    r.consistent = (st->n_hb_raw == o->acc[0] && st->n_coop == o->acc[1]) ? 1 : 0;
-    r.reserved = 0;
 }
 
 }  // namespace
@@ -471,40 +434,39 @@ hipError_t launch_met_domain(const LatticeArgs& a, uint32_t pass, hipStream_t s,
     }
 }
 
-hipError_t launch_recount(const LatticeArgs& a, int64_t* out, int spread, int with_counts, int step_gate,
-                          hipStream_t s)
+// Quads of four x-adjacent cells.  The observables' sums meet in a few
+// addresses, the counter slots are many.
+template <bool OBS>
+hipError_t recount_launch(const LatticeArgs& a, int64_t* out, int spread, const ObsArgs& o, hipStream_t s)
 {
-    if (!with_counts && a.L % 2 == 0) {               // column pairs: even L
-        // rows per wavefront for ~8192 wavefronts
-        const uint32_t groups = (a.L / 2 + 63) / 64;
-        const uint32_t wpg = groups >= 8192 ? 1 : 8192 / groups;
-        const uint32_t rows = (a.L + wpg - 1) / wpg;
-        const uint32_t segs = (a.L + rows - 1) / rows;
-        const dim3 grid(groups, (segs + 3) / 4);
-        recount_rows_kernel<<<grid, 256, 0, s>>>(a, out, spread, step_gate, rows);
-        return hipGetLastError();
-    }
-    recount_kernel<<<grid_for(a.N), kBlock, 0, s>>>(a, out, spread, with_counts, step_gate);
+    RecountShape sh;
+    sh.per_row = (a.L + 3) / 4;
+    sh.quads = sh.per_row * a.L;
+    sh.inv_row = 1.0 / (double)sh.per_row;
+    const uint32_t blocks = (sh.quads + kBlock - 1) / kBlock;
+    const uint32_t most = OBS ? kRecountBlocks : 2048u;
+    const uint32_t grid = blocks < most ? blocks : most;
+    if (a.L % 4 == 0) recount_kernel<4, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
+    else if (a.L % 2 == 0) recount_kernel<2, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
+    else recount_kernel<1, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
     return hipGetLastError();
+}
+
+hipError_t launch_recount(const LatticeArgs& a, int64_t* slots, hipStream_t s)
+{
+    return recount_launch<false>(a, slots, kSlots, ObsArgs{}, s);
+}
+
+hipError_t launch_obs(const LatticeArgs& a, const ObsArgs& o, hipStream_t s)
+{
+    return recount_launch<true>(a, o.obs->acc, kObsSpread, o, s);
 }
 
 hipError_t launch_state_counts(const LatticeArgs& a, int64_t* out, hipStream_t s)
 {
     const uint32_t nwords = a.N;                          // 4N bytes
-    state_counts_kernel<<<grid_for(nwords), kBlock, 0, s>>>(reinterpret_cast<const uint32_t*>(a.sigma), nwords, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_obs_zero(DevObs* o, hipStream_t s)
-{
-    obs_zero_kernel<<<1, 64, 0, s>>>(o);
-    return hipGetLastError();
-}
-
-hipError_t launch_obs_final(DevObs* o, const DevState* st, const DevTables* tab, double Nd, double J,
-                            double Jsigma, double P, double vHB, hipStream_t s)
-{
-    obs_final_kernel<<<1, 64, 0, s>>>(o, st, tab, Nd, J, Jsigma, P, vHB);
+    // at most kRecountBlocks workgroups, whose sums meet in six addresses
+    state_counts_kernel<<<grid_for(nwords) < kRecountBlocks ? grid_for(nwords) : kRecountBlocks, kBlock, 0, s>>>(reinterpret_cast<const uint32_t*>(a.sigma), nwords, out);
     return hipGetLastError();
 }
 

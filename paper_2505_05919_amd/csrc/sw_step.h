@@ -1,88 +1,7 @@
-// Swendsen-Wang step kernels and the lattice recount (included inside the
-// kernels' namespace).  The step kernels work on kTW x kTH-cell tiles; each
+// Swendsen-Wang step kernels (included inside the kernels' namespace).  The step kernels work on kTW x kTH-cell tiles; each
 // has a body shared by the single-chain kernel (grid = the chain's tiles) and
 // the batched kernel (workgroup -> chain and tile through prefix sums).
 #pragma once
-
-// ---------------------------------------------------------------------------
-// Recount of N_HB_raw and N_sigma for cell c (and the state counts N_q').
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void recount_cell(const LatticeArgs& a, uint32_t c, uint32_t x, uint32_t y, int& hb,
-                                             int& co, int* cnt)
-{
-    const uint32_t L = a.L;
-    const size_t N = a.N;
-    const uint8_t* __restrict__ s = a.sigma;
-    const uint32_t row = y * L;
-    const uint32_t xp = (x + 1 == L) ? 0 : x + 1;
-    const uint32_t rp = (y + 1 == L) ? 0 : row + L;
-    const int s0 = s[c], s1 = s[N + c], s2 = s[2 * N + c], s3 = s[3 * N + c];
-    hb += (s0 == s[N + xp + row]) + (s2 == s[3 * N + x + rp]);
-    co += (s0 == s1) + (s0 == s2) + (s0 == s3) + (s1 == s2) + (s1 == s3) + (s2 == s3);
-    if (cnt) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) cnt[k] += (s0 == k) + (s1 == k) + (s2 == k) + (s3 == k);
-    }
-}
-
-// Row-based recount (any even L): lane i owns the cells 2i, 2i+1 of the rows
-// of its wavefront; 16-bit loads of the four planes, wave-uniform row offsets.
-__device__ __forceinline__ uint32_t ld16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-{
-    return __builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
-}
-
-__global__ __launch_bounds__(256) void recount_rows_kernel(LatticeArgs a, int64_t* out, int spread, int step_gate,
-                                                           uint32_t rows)
-{
-    if (step_gate && a.st->skip) return;
-    const uint32_t L = a.L, N = a.N;
-    const uint32_t lane = threadIdx.x & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t pair = blockIdx.x * 64 + lane;
-    const uint32_t y0 = (blockIdx.y * 4 + wave) * rows;
-    int hb = 0, co = 0;
-    if (pair < (L >> 1) && y0 < L) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.sigma, 4 * N);
-        const uint32_t x = 2 * pair, xn = (x + 2 == L) ? 0 : x + 2;
-        const uint32_t y1 = min(y0 + rows, L);
-        for (uint32_t y = y0; y < y1; ++y) {
-            const uint32_t o = y * L, op = ((y + 1 == L) ? 0 : y + 1) * L;
-            const uint32_t d0 = ld16(rs, x, o), d1 = ld16(rs, x, o + N), d2 = ld16(rs, x, o + 2 * N),
-                           d3 = ld16(rs, x, o + 3 * N);
-            const uint32_t u3 = ld16(rs, x, 3 * N + op);           // arm 3 of the row above
-            const uint32_t n1 = ld8b(rs, xn, o + N);                // arm 1 of the cell right of the pair
-            const uint32_t a0 = d0 & 255, b0 = d0 >> 8, a1 = d1 & 255, b1 = d1 >> 8;
-            const uint32_t a2 = d2 & 255, b2 = d2 >> 8, a3 = d3 & 255, b3 = d3 >> 8;
-            hb += (a0 == b1) + (b0 == n1) + (a2 == (u3 & 255)) + (b2 == (u3 >> 8));
-            co += (a0 == a1) + (a0 == a2) + (a0 == a3) + (a1 == a2) + (a1 == a3) + (a2 == a3);
-            co += (b0 == b1) + (b0 == b2) + (b0 == b3) + (b1 == b2) + (b1 == b3) + (b2 == b3);
-        }
-    }
-    const int v[2] = {hb, co};
-    block_add<2>(v, out + ((blockIdx.x + blockIdx.y * gridDim.x) & (spread - 1)), spread);
-}
-
-__global__ __launch_bounds__(kBlock) void recount_kernel(LatticeArgs a, int64_t* out, int spread, int with_counts,
-                                                         int step_gate)
-{
-    if (step_gate && a.st->skip) return;
-    const double inv_L = 1.0 / (double)a.L;
-    int hb = 0, co = 0;
-    int cnt[6] = {0, 0, 0, 0, 0, 0};
-    for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < a.N; c += gridDim.x * kBlock) {
-        uint32_t x;
-        const uint32_t y = divmod(c, a.L, inv_L, x);
-        recount_cell(a, c, x, y, hb, co, with_counts ? cnt : nullptr);
-    }
-    if (with_counts) {
-        const int v[8] = {hb, co, cnt[0], cnt[1], cnt[2], cnt[3], cnt[4], cnt[5]};
-        block_add<8>(v, out, 1);
-    } else {
-        const int v[2] = {hb, co};
-        block_add<2>(v, out + (blockIdx.x & (spread - 1)), spread);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Swendsen-Wang (Sec. II.D).

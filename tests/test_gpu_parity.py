@@ -257,3 +257,23 @@ def test_keep_sigma_resume(cvf, oracle_mod):
     for k in ("n_hb_raw", "n_coop", "count"):
         assert og[k] == oo[k]
     ch.close()
+
+
+@pytest.mark.parametrize("L", [2, 3, 4, 5, 6, 7, 30, 724, 726, 727, 1449])
+def test_recount_of_the_lattice(cvf, L):
+    """The observables' recount against numpy on the same configuration: rows
+    of every length modulo a quad (one to four cells at the end, dword, half
+    word and byte rows), one workgroup up to several quads per lane, twice in
+    a row (the accumulators are cleared in between)."""
+    p = cvf.cvf_params_from_si(300.0, 0.1, L=L, seed=1200 + L)
+    say(f"case recount L={L}")
+    ch = cvf.Chain(p, cvf.CVF_ALGO_METROPOLIS)
+    s = ch.sigma.cpu().numpy().reshape(4, L, L)
+    hb = int((s[0] == np.roll(s[1], -1, axis=1)).sum() + (s[2] == np.roll(s[3], -1, axis=0)).sum())
+    co = sum(int((s[a] == s[b]).sum()) for a in range(4) for b in range(a + 1, 4))
+    for _ in range(2):
+        o = ch.obs()
+        assert (o["n_hb_raw"], o["n_coop"]) == (hb, co)
+        assert o["count"] == [int((s == k).sum()) for k in range(6)]
+        assert o["consistent"] == 1
+    ch.close()
