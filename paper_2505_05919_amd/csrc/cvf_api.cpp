@@ -309,10 +309,13 @@ int cvf_metropolis_sweeps(cvf_state* st, int64_t nsweeps, void* stream)
     VolArgs v = st->va;
     v.mode = kVolMet;
     v.met_att_add = 4 * (int64_t)st->N;
+    // the first step is opened by a launch of its own, each later one by the
+    // last launch of the step before
+    if (nsweeps > 0) TIMED(CVF_K_VOLUME, launch_volume, v, s);
     for (int64_t i = 0; i < nsweeps; ++i) {
-        TIMED(CVF_K_VOLUME, launch_volume, v, s);
-        TIMED(CVF_K_MET_SWEEP, launch_met_colour, st->la, 0, s);
-        TIMED(CVF_K_MET_SWEEP, launch_met_colour, st->la, 1, s);
+        const StepCtl c = {(uint32_t)(i & 1), 0}, last = {c.bank, i + 1 < nsweeps ? 1u : 0u};
+        TIMED(CVF_K_MET_SWEEP, launch_met_colour, st->la, v, c, 0, s);
+        TIMED(CVF_K_MET_SWEEP, launch_met_colour, st->la, v, last, 1, s);
     }
     return CVF_OK;
 }
@@ -324,10 +327,12 @@ int cvf_metropolis_domain_sweeps(cvf_state* st, int64_t nsweeps, void* stream)
     VolArgs v = st->va;
     v.mode = kVolMet;
     v.met_att_add = 4 * (int64_t)st->N;
-    for (int64_t i = 0; i < nsweeps; ++i) {
-        TIMED(CVF_K_VOLUME, launch_volume, v, s);
-        for (uint32_t pass = 0; pass < 4; ++pass) TIMED(CVF_K_MET_DOMAIN, launch_met_domain, st->la, pass, s);
-    }
+    if (nsweeps > 0) TIMED(CVF_K_VOLUME, launch_volume, v, s);
+    for (int64_t i = 0; i < nsweeps; ++i)
+        for (uint32_t pass = 0; pass < 4; ++pass) {
+            const StepCtl c = {(uint32_t)(i & 1), pass == 3 && i + 1 < nsweeps ? 1u : 0u};
+            TIMED(CVF_K_MET_DOMAIN, launch_met_domain, st->la, v, c, pass, s);
+        }
     return CVF_OK;
 }
 
@@ -339,10 +344,11 @@ int cvf_sw_steps(cvf_state* st, int64_t nsteps, void* stream)
     hipStream_t s = (hipStream_t)stream;
     VolArgs v = st->va;
     v.mode = kVolSw;
+    if (nsteps > 0) TIMED(CVF_K_VOLUME, launch_volume, v, s);
     for (int64_t i = 0; i < nsteps; ++i) {
-        TIMED(CVF_K_VOLUME, launch_volume, v, s);
-        TIMED(CVF_K_SW_BONDS, launch_sw_tiles, st->la, s);
-        TIMED(CVF_K_SW_FLIP, launch_sw_flip_tiles, st->la, s);
+        const StepCtl c = {(uint32_t)(i & 1), 0}, last = {c.bank, i + 1 < nsteps ? 1u : 0u};
+        TIMED(CVF_K_SW_BONDS, launch_sw_tiles, st->la, v, c, s);
+        TIMED(CVF_K_SW_FLIP, launch_sw_flip_tiles, st->la, v, last, s);
     }
     return CVF_OK;
 }
@@ -573,12 +579,16 @@ int batch_upload(cvf_batch* b, hipStream_t s, uint8_t* staging)
     return hip_status(e);
 }
 
-hipError_t batch_sweep(cvf_batch* b, hipStream_t s)
+// n sweeps of every chain (see cvf_metropolis_sweeps).
+hipError_t batch_sweeps(cvf_batch* b, int64_t n, hipStream_t s)
 {
     const uint32_t count = (uint32_t)b->chains.size();
-    hipError_t e = launch_volume_batch(b->d_ent, count, kVolMet, s);
-    if (e == hipSuccess) e = launch_met_batch(b->d_ent, b->d_start, count, b->total_blocks, b->q, 0, b->le, s);
-    if (e == hipSuccess) e = launch_met_batch(b->d_ent, b->d_start, count, b->total_blocks, b->q, 1, b->le, s);
+    hipError_t e = n > 0 ? launch_volume_batch(b->d_ent, count, kVolMet, s) : hipSuccess;
+    for (int64_t i = 0; e == hipSuccess && i < n; ++i) {
+        const StepCtl c = {(uint32_t)(i & 1), 0}, last = {c.bank, i + 1 < n ? 1u : 0u};
+        e = launch_met_batch(b->d_ent, b->d_start, count, b->total_blocks, b->q, 0, b->le, c, s);
+        if (e == hipSuccess) e = launch_met_batch(b->d_ent, b->d_start, count, b->total_blocks, b->q, 1, b->le, last, s);
+    }
     return e;
 }
 
@@ -588,7 +598,7 @@ int batch_capture(cvf_batch* b, int32_t block)
     if (!b->capture && hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking) != hipSuccess) return CVF_EHIP;
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal);
-    for (int32_t i = 0; e == hipSuccess && i < block; ++i) e = batch_sweep(b, b->capture);
+    if (e == hipSuccess) e = batch_sweeps(b, block, b->capture);
     hipError_t e2 = hipStreamEndCapture(b->capture, &g);
     if (e == hipSuccess) e = e2;
     if (e == hipSuccess) e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
@@ -687,9 +697,7 @@ int cvf_batch_metropolis_sweeps(cvf_batch* b, int64_t nsweeps, int32_t graph_blo
         for (; done + graph_block <= nsweeps; done += graph_block)
             if (hipGraphLaunch(b->exec, s) != hipSuccess) return CVF_EHIP;
     }
-    for (; done < nsweeps; ++done)
-        if (batch_sweep(b, s) != hipSuccess) return CVF_EHIP;
-    return CVF_OK;
+    return hip_status(batch_sweeps(b, nsweeps - done, s));
 }
 
 int cvf_batch_sw_steps(cvf_batch* b, int64_t nsteps, void* stream)
@@ -698,13 +706,13 @@ int cvf_batch_sw_steps(cvf_batch* b, int64_t nsteps, void* stream)
     if (!b->has_sw) return CVF_ENOMEM;
     hipStream_t s = (hipStream_t)stream;
     const uint32_t count = (uint32_t)b->chains.size();
-    for (int64_t i = 0; i < nsteps; ++i) {
-        hipError_t e = launch_volume_batch(b->d_ent, count, kVolSw, s);
-        if (e == hipSuccess) e = launch_sw_batch(b->d_ent, b->d_tstart, count, b->sw_tiles, 0, s);
-        if (e == hipSuccess) e = launch_sw_batch(b->d_ent, b->d_tstart, count, b->sw_tiles, 2, s);
-        if (e != hipSuccess) return CVF_EHIP;
+    hipError_t e = nsteps > 0 ? launch_volume_batch(b->d_ent, count, kVolSw, s) : hipSuccess;
+    for (int64_t i = 0; e == hipSuccess && i < nsteps; ++i) {
+        const StepCtl c = {(uint32_t)(i & 1), 0}, last = {c.bank, i + 1 < nsteps ? 1u : 0u};
+        e = launch_sw_batch(b->d_ent, b->d_tstart, count, b->sw_tiles, 0, c, s);
+        if (e == hipSuccess) e = launch_sw_batch(b->d_ent, b->d_tstart, count, b->sw_tiles, 2, last, s);
     }
-    return CVF_OK;
+    return hip_status(e);
 }
 
 int cvf_batch_autotune(cvf_batch* b, int32_t sweeps, void* stream, int32_t* rows_out)
@@ -723,16 +731,14 @@ int cvf_batch_autotune(cvf_batch* b, int32_t sweeps, void* stream, int32_t* rows
     // one untimed block first (clocks and caches settle), then two timed
     // rounds over the candidates; each keeps its faster time
     int rc = cvf_batch_set_rows(b, cand[0], stream);
-    for (int32_t k = 0; k < sweeps && rc == CVF_OK; ++k)
-        if (batch_sweep(b, s) != hipSuccess) rc = CVF_EHIP;
+    if (rc == CVF_OK) rc = hip_status(batch_sweeps(b, sweeps, s));
     float t_min[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
     for (int round = 0; round < 2 && rc == CVF_OK; ++round) {
         for (int i = 0; i < 5 && rc == CVF_OK; ++i) {
             rc = cvf_batch_set_rows(b, cand[i], stream);
             if (rc) break;
             if (hipEventRecord(e0, s) != hipSuccess) { rc = CVF_EHIP; break; }
-            for (int32_t k = 0; k < sweeps && rc == CVF_OK; ++k)
-                if (batch_sweep(b, s) != hipSuccess) rc = CVF_EHIP;
+            rc = hip_status(batch_sweeps(b, sweeps, s));
             float ms = 0.f;
             if (rc == CVF_OK && (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                                  hipEventElapsedTime(&ms, e0, e1) != hipSuccess))

@@ -18,9 +18,12 @@ constexpr uint32_t kStreamSwf = 4;    // Swendsen-Wang cluster shift
 constexpr uint32_t kStreamOrd = 5;    // arm-domain sweep: pass order
 constexpr uint32_t kStreamDom = 6;    // arm-domain sweep: proposal + acceptance
 
-// Per-workgroup partial sums are spread over this many int64 slots so that
-// same-address atomics do not serialise; the volume kernel folds them.
-constexpr int kSlots = 256;
+// Per-workgroup partial sums (d N_HB_raw, d N_sigma, accepted) are spread over
+// this many int64 slots so that same-address atomics do not serialise.  Two
+// banks [bank][value][slot]: a Metropolis step's first launch adds to bank 0,
+// its other launches to bank 1; Swendsen-Wang steps recount into the banks in
+// turn.  The volume kernel folds both.
+constexpr int kSlots = 128, kBankSlots = 3 * kSlots;
 
 // Swendsen-Wang tiles: kTW x kTH cells per workgroup (the last tile of a row
 // or column is ragged).  Per tile the bond kernel keeps, for the step's
@@ -33,6 +36,26 @@ constexpr uint32_t kTW = 64, kTH = CVF_SW_TILE_H, kTC = kTW * kTH;
 constexpr uint32_t kTT = kTC / 4;        // threads of a tile workgroup: 4 cells, 16 bond indices each
 constexpr uint32_t kEdgeBytes = kTW + kTH;
 
+// A step as its launches see it.  theta is what the step's first launch starts
+// from; with pending set, the volume move proposes to cross v = 2 and needs
+// N_HB_raw, which the first launch works out (see open_step).  theta2: the
+// theta of the step's other launches.
+struct StepView {
+    int32_t skip;            // 1: the step limit is reached, the launches do nothing
+    int32_t theta, theta2;
+    uint32_t t_cur;          // Philox counter word 1
+    int32_t pending;
+    int32_t pad;
+};
+
+// The volume move of a pending step.
+struct PendingMove {
+    double v0, u0, v1, u1;
+    int64_t n_hb;            // N_HB_raw without the slots of bank 1 (Metropolis) or of both (SW)
+    uint32_t word;           // acceptance word
+    int32_t th0, th1, pad;
+};
+
 // Mutable per-chain scalars, at offset 0 of the workspace.
 struct DevState {
     int64_t t_next;          // index of the next MC step
@@ -41,11 +64,11 @@ struct DevState {
     int64_t met_att, met_acc, vol_att, vol_acc;
     double v;                // v_iso / v0
     double u;                // u_LJ(v), cached: the volume move needs u(v) and u(v')
-    uint32_t t_cur;          // step being executed (Philox counter word 1)
     int32_t theta;           // 1 liquid (v < 2), 0 gas
     int32_t sw_done;         // a Swendsen-Wang step has produced labels
-    int32_t skip;            // 1: the step limit is reached, step kernels do nothing
     int64_t stop_at;         // no step with index >= stop_at is performed
+    StepView view[2];        // the steps of a call, in turn
+    PendingMove pend;
 };
 
 // Host-computed constants copied to the workspace at init.
@@ -68,7 +91,7 @@ struct DevObs {
 // Workspace layout (byte offsets, all 256-aligned).
 constexpr size_t kOffState = 0;
 constexpr size_t kOffSlots = 256;
-constexpr size_t kOffTables = kOffSlots + 3 * kSlots * sizeof(int64_t);   // 6400
+constexpr size_t kOffTables = kOffSlots + 2 * kBankSlots * sizeof(int64_t);   // 6400
 constexpr size_t kOffObs = kOffTables + 768;                                // 7168
 constexpr size_t kBaseBytes = kOffObs + 512;                                // 7680
 
@@ -157,13 +180,16 @@ struct BatchEntry {
     double upr_inv;          // 1 / upr
     uint32_t iters;          // units per lane
     uint32_t blocks;         // workgroups of this chain: ceil(units / (256 iters))
-    // The chain's step as the batched volume kernel opened it (device-written
-    // before every sweep's colour passes, which read it with the entry instead
-    // of following la.st)
-    int32_t skip;
-    int32_t theta;
-    uint32_t t_cur;
-    uint32_t pad;
+    // The chain's steps as the batched launches open them (device-written; the
+    // colour passes read them with the entry instead of following la.st)
+    StepView view[2];
+};
+
+// Which of a call's steps a launch belongs to (bank = step index mod 2), and
+// whether it also opens the next one (its volume move, by workgroups of its
+// own) into the other bank.
+struct StepCtl {
+    uint32_t bank, open;
 };
 
 // Launchers (cvf_kernels.hip).  Each returns the launch status.
@@ -176,9 +202,11 @@ hipError_t launch_tables_init(DevTables* dst, const DevTables& src, hipStream_t 
 hipError_t noalloc_scratch(void** ptr);
 hipError_t launch_sigma_init(const LatticeArgs& a, hipStream_t s);
 hipError_t launch_volume(const VolArgs& a, hipStream_t s, DispatchEvents ev = {});
-hipError_t launch_met_colour(const LatticeArgs& a, int colour, hipStream_t s, DispatchEvents ev = {});
+hipError_t launch_met_colour(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, hipStream_t s,
+                             DispatchEvents ev = {});
 // Arm-domain sweep: pass 0..3 of the step's drawn arm order (any L >= 2).
-hipError_t launch_met_domain(const LatticeArgs& a, uint32_t pass, hipStream_t s, DispatchEvents ev = {});
+hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t pass, hipStream_t s,
+                             DispatchEvents ev = {});
 // N_HB_raw and N_sigma of the lattice added to the counter slots.
 hipError_t launch_recount(const LatticeArgs& a, int64_t* slots, hipStream_t s);
 // The recount with state counts and the observables record, after a volume
@@ -189,21 +217,22 @@ hipError_t launch_state_counts(const LatticeArgs& a, int64_t* out, hipStream_t s
 // Tiled SW step: bonds + in-tile unions + the tile-crossing links (each
 // united by the later of its two tiles), then the cluster shift fused with
 // the recount.  Labels are written out on request.
-hipError_t launch_sw_tiles(const LatticeArgs& a, hipStream_t s, DispatchEvents ev = {});
+hipError_t launch_sw_tiles(const LatticeArgs& a, const VolArgs& v, StepCtl c, hipStream_t s, DispatchEvents ev = {});
 // Zero the edge arrival counters (once, when the chain is created).
 hipError_t launch_sw_counters_init(const LatticeArgs& a, hipStream_t s);
-hipError_t launch_sw_flip_tiles(const LatticeArgs& a, hipStream_t s, DispatchEvents ev = {});
+hipError_t launch_sw_flip_tiles(const LatticeArgs& a, const VolArgs& v, StepCtl c, hipStream_t s,
+                                DispatchEvents ev = {});
 hipError_t launch_sw_labels(const LatticeArgs& a, uint32_t* out, hipStream_t s);
 // Batched Metropolis: `ent` / `start` are device arrays (count entries,
 // count+1 prefix sums of workgroups); all chains share q; le: every chain's
 // table allows the one-compare acceptance.
-hipError_t launch_met_batch(const BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks,
-                            int q, int colour, int le, hipStream_t s);
+hipError_t launch_met_batch(BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks, int q,
+                            int colour, int le, StepCtl c, hipStream_t s);
 hipError_t launch_volume_batch(BatchEntry* ent, uint32_t count, int mode, hipStream_t s);
 // Batched Swendsen-Wang stage: 0 tiles (bonds, in-tile unions and the
 // tile-crossing links), 2 shift + recount; start: count+1 prefix sums of the
 // per-chain tiles.
-hipError_t launch_sw_batch(const BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks,
-                           int stage, hipStream_t s);
+hipError_t launch_sw_batch(BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks, int stage,
+                           StepCtl c, hipStream_t s);
 
 }  // namespace cvf

@@ -104,7 +104,7 @@ __device__ double lj_energy(double v, const double* r2)
 __global__ void state_init_kernel(DevState* st, int64_t* slots, const DevTables* tab, double v_init)
 {
     const int i = threadIdx.x;
-    for (int k = i; k < 3 * kSlots; k += blockDim.x) slots[k] = 0;
+    for (int k = i; k < 2 * kBankSlots; k += blockDim.x) slots[k] = 0;
     if (i == 0) {
         st->t_next = 0;
         st->n_hb_raw = 0;
@@ -112,10 +112,8 @@ __global__ void state_init_kernel(DevState* st, int64_t* slots, const DevTables*
         st->met_att = st->met_acc = st->vol_att = st->vol_acc = 0;
         st->v = v_init;
         st->u = lj_energy(v_init, tab->r2);
-        st->t_cur = 0;
         st->theta = v_init < 2.0 ? 1 : 0;
         st->sw_done = 0;
-        st->skip = 0;
         st->stop_at = INT64_MAX;
     }
 }
@@ -133,48 +131,150 @@ __global__ __launch_bounds__(kBlock) void sigma_init_kernel(LatticeArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Volume move + counter fold: one wavefront.  Folds the per-workgroup slots
-// of the previous sigma update into the totals, opens step t, and performs
-// the Metropolis move of v_iso (Sec. II.B step 1) with the full dH of
-// Eq. (1) and (3):  N (u(v') - u(v)) + P N (v' - v)
-//                   + (theta(v') - theta(v)) (P v_HB - J) N_HB_raw.
-// u(v) of the current volume is cached; the shell terms of u(v') are
-// evaluated one per lane and summed by lane 0 in ascending shell order, the
-// same order as the sequential definition.
+// Volume move: one wavefront opens a step -- the Metropolis move of v_iso
+// (Sec. II.B step 1) with the full dH of Eq. (1) and (3),
+//   N (u(v') - u(v)) + P N (v' - v) + (theta(v') - theta(v)) (P v_HB - J) N_HB_raw.
+// While theta stays what it is, N_HB_raw drops out and the move needs nothing
+// of the sigma update before it.  So only the first step of a call is opened
+// by a launch of its own (volume_step, which also folds the counter slots);
+// every later one is opened by a workgroup of the last launch of the step
+// before it (open_next), beside the sigma update: the launch it saves is
+// 4.8 us of a step.  A move that would cross v = 2 is left pending, and the
+// step's first launch decides it (resolve_step) from N_HB_raw, which by then
+// is complete: every workgroup for itself, the first one writing the result.
 // ---------------------------------------------------------------------------
-// Executed by one full wavefront (lanes 0..63); `term` is 40 doubles of LDS.
-// Every global load is issued before the first store, so the whole move
-// costs one memory round trip.  `out` (batches): the batch entry that also
-// receives the opened step (skip, theta, step index).
-__device__ void volume_step(const VolArgs& a, double* term, BatchEntry* out = nullptr)
+struct VolState {
+    int64_t t_next, stop_at, met_att, vol_att, vol_acc;
+    double v, u, r2;
+    int theta;
+};
+
+__device__ __forceinline__ VolState vol_load(const VolArgs& a, int lane)
 {
+    const DevState* st = a.st;
+    VolState s;
+    s.t_next = st->t_next;
+    s.stop_at = st->stop_at;
+    s.met_att = st->met_att;
+    s.vol_att = st->vol_att;
+    s.vol_acc = st->vol_acc;
+    s.v = st->v;
+    s.u = st->u;
+    s.theta = st->theta;
+    s.r2 = lane < 40 ? a.tab->r2[lane] : 0.0;
+    return s;
+}
+
+// dH of the move and the acceptance through the word w; the same operations
+// in the same order wherever a move is decided.
+__device__ __forceinline__ bool vol_accept(const VolArgs& a, double v0, double u0, int th0, double v1, double u1, int th1,
+                                           int64_t n_hb, uint32_t w)
+{
+    const double dH = (a.Nd * (u1 - u0)) + ((a.P * a.Nd) * (v1 - v0)) +
+                      (((double)(th1 - th0) * (a.P * a.vHB - a.J)) * (double)n_hb);
+    return dH <= 0.0 || ((double)w + 0.5) * (1.0 / 4294967296.0) < exp(-a.beta * dH);
+}
+
+// Opens the step s.t_next into view, by one wavefront; `term` is 40 doubles of
+// LDS.  The shell terms of u(v') are evaluated one per lane and summed by lane
+// 0 in ascending shell order, the order of the sequential definition.
+// known: n_hb is N_HB_raw; otherwise a move that crosses v = 2 is left
+// pending, n_hb being the part of N_HB_raw that is complete now (lane 0's).
+__device__ __forceinline__ void open_step(const VolArgs& a, const VolState& s, double* term, StepView* view, bool known,
+                                          int64_t n_hb, int lane)
+{
+    DevState* st = a.st;
+    if (s.t_next >= s.stop_at) {                     // step limit: the step's launches do nothing
+        if (lane == 0) {
+            view->skip = 1;
+            view->pending = 0;
+        }
+        return;
+    }
+    const uint32_t t = (uint32_t)s.t_next;
+    const uint4 w = philox(0u, t, 0u, kStreamVol, a.key0, a.key1);
+    const double x = (double)((int64_t)2 * (int64_t)w.x + 1 - 4294967296LL) * (1.0 / 4294967296.0);
+    const double v1 = s.v + a.dv_max * x;
+    const bool inside = a.do_volume && v1 >= 1.0;
+    if (inside && lane >= 1 && lane <= 36) {
+        const double d2 = v1 * (double)lane;
+        const double s6 = 1.0 / (d2 * d2 * d2);
+        term[lane] = s.r2 * (s6 * s6 - s6);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if (lane != 0) return;
+    double v = s.v, u = s.u;
+    int th = s.theta, pending = 0;
+    int64_t vatt = s.vol_att, vacc = s.vol_acc;
+    if (a.do_volume) {
+        vatt += 1;
+        if (inside) {
+            // six shell terms read at a time, then added in ascending m
+            // while v' m <= 36 (v' >= 1, so the condition fails past m = 36;
+            // it is monotone in m, so the terms added and their order are
+            // those of the loop that stops at the first failing m)
+            double sum = 0.0;
+#pragma unroll 1
+            for (int m0 = 1; m0 <= 36; m0 += 6) {
+                double tm[6];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) tm[k] = term[m0 + k];
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
+                    if (v1 * (double)(m0 + k) <= 36.0) sum = sum + tm[k];
+            }
+            const double u1 = 2.0 * sum;
+            const int th1 = v1 < 2.0 ? 1 : 0;
+            if (!known && th1 != s.theta) {
+                st->pend = {s.v, s.u, v1, u1, n_hb, w.y, s.theta, th1, 0};
+                pending = 1;
+            } else if (vol_accept(a, s.v, s.u, s.theta, v1, u1, th1, known ? n_hb : 0, w.y)) {
+                v = v1;
+                u = u1;
+                th = th1;
+                vacc += 1;
+            }
+        }
+    }
+    *view = {0, th, th, t, pending, 0};
+    st->t_next = s.t_next + 1;
+    st->met_att = s.met_att + a.met_att_add;
+    st->vol_att = vatt;
+    st->vol_acc = vacc;
+    st->v = v;
+    st->u = u;
+    st->theta = th;
+}
+
+// First step of a call, by one wavefront: folds the counter slots of the calls
+// before it into the totals and opens the step with N_HB_raw known.  Every
+// global load is issued before the first store.  kVolFold: the fold alone,
+// and the observables' accumulators cleared for the recount that follows.
+__device__ void volume_step(const VolArgs& a, double* term, StepView* view)
+{
+    constexpr int kPer = 2 * kSlots / 64;
     const int lane = threadIdx.x & 63;
     DevState* st = a.st;
-    int64_t sl[3][kSlots / 64];
+    int64_t sl[3][kPer];
 #pragma unroll
     for (int j = 0; j < 3; ++j)
 #pragma unroll
-        for (int k = 0; k < kSlots / 64; ++k) sl[j][k] = a.slots[j * kSlots + k * 64 + lane];
-    const int64_t t_next = st->t_next, stop_at = st->stop_at;
-    const int64_t hb0 = st->n_hb_raw, co0 = st->n_coop, macc0 = st->met_acc, matt0 = st->met_att;
-    const int64_t vatt0 = st->vol_att, vacc0 = st->vol_acc;
-    const double v0 = st->v, u0 = st->u;
-    const int th0 = st->theta;
-    const double r2 = lane < 40 ? a.tab->r2[lane] : 0.0;
-    int64_t hb = 0, co = 0, ac = 0;
-#pragma unroll
-    for (int k = 0; k < kSlots / 64; ++k) {
-        hb += sl[0][k];
-        co += sl[1][k];
-        ac += sl[2][k];
-    }
+        for (int k = 0; k < kPer; ++k) {
+            const int b = k / (kSlots / 64), i = k % (kSlots / 64);
+            sl[j][k] = a.slots[b * kBankSlots + j * kSlots + i * 64 + lane];
+        }
+    const VolState s = vol_load(a, lane);
+    const int64_t hb0 = st->n_hb_raw, co0 = st->n_coop, macc0 = st->met_acc;
+    int64_t r[3] = {0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 3; ++j)
 #pragma unroll
-        for (int k = 0; k < kSlots / 64; ++k) a.slots[j * kSlots + k * 64 + lane] = 0;
+        for (int k = 0; k < kPer; ++k) r[j] += sl[j][k];
+    for (int k = lane; k < 2 * kBankSlots; k += 64) a.slots[k] = 0;
     // the three sums in one butterfly: each step's six 32-bit exchanges are
     // issued together and waited for once
-    int64_t r[3] = {hb, co, ac};
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         int64_t x[3];
@@ -183,94 +283,89 @@ __device__ void volume_step(const VolArgs& a, double* term, BatchEntry* out = nu
 #pragma unroll
         for (int j = 0; j < 3; ++j) r[j] += x[j];
     }
-    const int64_t n_hb = hb0 + r[0];
-    const int64_t n_co = co0 + r[1];
-    const int64_t m_acc = macc0 + r[2];
-    if (a.mode == kVolFold) {                        // observables follow: clear their accumulators
+    const int64_t n_hb = hb0 + r[0], n_co = co0 + r[1];
+    const bool fold = a.mode == kVolFold, stop = fold || s.t_next >= s.stop_at;
+    if (fold) {
         DevObs* obs = (DevObs*)((char*)st - kOffState + kOffObs);
         if (lane < kObsAcc) obs->acc[lane] = 0;
         if (lane == 0) obs->arrived = 0;
     }
-    if (a.mode == kVolFold || t_next >= stop_at) {   // fold only; at the step limit the step kernels skip
-        if (lane == 0) {
-            st->n_hb_raw = n_hb;
-            st->n_coop = n_co;
-            st->met_acc = m_acc;
-            if (a.mode != kVolFold) st->skip = 1;
-            if (out) out->skip = 1;
-        }
-        return;
+    if (lane == 0) {
+        st->met_acc = macc0 + r[2];
+        const bool sw = a.mode == kVolSw && !stop;   // the SW step ends with a full recount
+        st->n_hb_raw = sw ? 0 : n_hb;
+        st->n_coop = sw ? 0 : n_co;
     }
-    const uint32_t t = (uint32_t)t_next;
-    const uint4 w = philox(0u, t, 0u, kStreamVol, a.key0, a.key1);
-    const double u = (double)((int64_t)2 * (int64_t)w.x + 1 - 4294967296LL) * (1.0 / 4294967296.0);
-    const double v1 = v0 + a.dv_max * u;
-    const bool inside = a.do_volume && v1 >= 1.0;
-    if (inside && lane >= 1 && lane <= 36) {
-        const double d2 = v1 * (double)lane;
-        const double s6 = 1.0 / (d2 * d2 * d2);
-        term[lane] = r2 * (s6 * s6 - s6);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    if (lane != 0) return;
-    double v = v0, uu = u0;
-    int th = th0;
-    int64_t vatt = vatt0, vacc = vacc0;
-    if (a.do_volume) {
-        vatt += 1;
-        if (inside) {
-            // all 36 shell terms read first, then added in ascending m while
-            // v' m <= 36 (v' >= 1, so the condition fails past m = 36; it is
-            // monotone in m, so the terms added and their order are those of
-            // the loop that stops at the first failing m)
-            double tm[36];
+    if (!fold) open_step(a, s, term, view, true, n_hb, lane);
+}
+
+// A later step of a call, opened beside the last launch of the step before it
+// by the wavefronts that call this (the first one of the workgroup in a
+// single-chain launch).  A pending Metropolis move first takes the slots of
+// bank 0, complete since the step's first launch, into the total, so that the
+// first launch of the next step finds the rest of N_HB_raw in bank 1 while it
+// adds to bank 0 itself.  An SW step's recount lies in one bank.
+__device__ void open_next(const VolArgs& a, double* term, StepView* view)
+{
+    const int lane = threadIdx.x & 63;
+    DevState* st = a.st;
+    const VolState s = vol_load(a, lane);
+    const double far = s.theta ? 2.0 - s.v : s.v - 2.0;
+    int64_t n_hb = 0;
+    // uniform: the move may cross (it is less than dv_max, and v' is rounded by
+    // less than another dv_max where that matters)
+    if (a.do_volume && far <= 2.0 * a.dv_max) {
+        n_hb = st->n_hb_raw;
+        if (a.mode == kVolMet) {
+            int64_t r[3];
 #pragma unroll
-            for (int m = 1; m <= 36; ++m) tm[m - 1] = term[m];
-            double sum = 0.0;
-#pragma unroll
-            for (int m = 1; m <= 36; ++m)
-                if (v1 * (double)m <= 36.0) sum = sum + tm[m - 1];
-            const double u1 = 2.0 * sum;
-            const int th1 = v1 < 2.0 ? 1 : 0;
-            const double dH = (a.Nd * (u1 - u0))
-                            + ((a.P * a.Nd) * (v1 - v0))
-                            + (((double)(th1 - th0) * (a.P * a.vHB - a.J)) * (double)n_hb);
-            bool acc = dH <= 0.0;
-            if (!acc) acc = ((double)w.y + 0.5) * (1.0 / 4294967296.0) < exp(-a.beta * dH);
-            if (acc) {
-                v = v1;
-                uu = u1;
-                th = th1;
-                vacc += 1;
+            for (int j = 0; j < 3; ++j) {
+                r[j] = 0;
+                for (int k = lane; k < kSlots; k += 64) {
+                    r[j] += a.slots[j * kSlots + k];
+                    a.slots[j * kSlots + k] = 0;
+                }
+                r[j] = wave_sum64(r[j]);
+            }
+            n_hb += r[0];
+            if (lane == 0) {
+                st->n_hb_raw = n_hb;
+                st->n_coop += r[1];
+                st->met_acc += r[2];
             }
         }
     }
-    st->skip = 0;
-    st->t_cur = t;
-    if (out) {
-        out->skip = 0;
-        out->theta = th;
-        out->t_cur = t;
+    open_step(a, s, term, view, false, n_hb, lane);
+}
+
+// The theta of a pending step, worked out by every wavefront of the step's
+// first launch; `commit` (the workgroup that writes it down).
+__device__ int resolve_step(const VolArgs& a, StepView* view, bool sw, bool commit)
+{
+    const int lane = threadIdx.x & 63;
+    DevState* st = a.st;
+    const PendingMove p = st->pend;
+    int64_t n = 0;
+    for (int k = lane; k < kSlots; k += 64) n += a.slots[kBankSlots + k] + (sw ? a.slots[k] : 0);
+    n = wave_sum64(n) + p.n_hb;
+    const bool acc = vol_accept(a, p.v0, p.u0, p.th0, p.v1, p.u1, p.th1, n, p.word);
+    const int th = acc ? p.th1 : p.th0;
+    if (commit && threadIdx.x == 0) {
+        view->theta2 = th;
+        if (acc) {
+            st->v = p.v1;
+            st->u = p.u1;
+            st->theta = th;
+            st->vol_acc += 1;
+        }
     }
-    st->t_next = t_next + 1;
-    st->met_att = matt0 + a.met_att_add;
-    st->met_acc = m_acc;
-    st->vol_att = vatt;
-    st->vol_acc = vacc;
-    st->v = v;
-    st->u = uu;
-    st->theta = th;
-    const bool sw = a.mode == kVolSw;            // the SW step ends with a full recount
-    st->n_hb_raw = sw ? 0 : n_hb;
-    st->n_coop = sw ? 0 : n_co;
+    return __builtin_amdgcn_readfirstlane(th);
 }
 
 __global__ __launch_bounds__(64) void volume_kernel(VolArgs a)
 {
     __shared__ double term[40];
-    volume_step(a, term);
+    volume_step(a, term, a.st->view);
 }
 
 #include "met_sweep.h"
@@ -321,43 +416,48 @@ hipError_t launch_volume(const VolArgs& a, hipStream_t s, DispatchEvents ev)
     return go(volume_kernel, dim3(1), dim3(64), s, ev, a);
 }
 
+// A launch that opens the next step has one more row of workgroups, whose
+// first one does it.
 template <int Q, bool R, bool LE>
-hipError_t launch_quad_r(const LatticeArgs& a, int colour, dim3 grid, hipStream_t s, const DispatchEvents& ev)
+hipError_t launch_quad_r(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, dim3 grid, hipStream_t s,
+                         const DispatchEvents& ev)
 {
-    if (colour == 0) return go(met_sweep4_kernel<Q, 0, R, LE>, grid, dim3(256), s, ev, a);
-    return go(met_sweep4_kernel<Q, 1, R, LE>, grid, dim3(256), s, ev, a);
+    if (colour == 0) return go(met_sweep4_kernel<Q, 0, R, LE>, grid, dim3(256), s, ev, a, v, c);
+    return go(met_sweep4_kernel<Q, 1, R, LE>, grid, dim3(256), s, ev, a, v, c);
 }
 
 template <int Q>
-hipError_t launch_quad(const LatticeArgs& a, int colour, dim3 grid, hipStream_t s, const DispatchEvents& ev)
+hipError_t launch_quad(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, dim3 grid, hipStream_t s,
+                       const DispatchEvents& ev)
 {
     if (a.quad == 2) {
-        if (a.met_le) return launch_quad_r<Q, true, true>(a, colour, grid, s, ev);
-        return launch_quad_r<Q, true, false>(a, colour, grid, s, ev);
+        if (a.met_le) return launch_quad_r<Q, true, true>(a, v, c, colour, grid, s, ev);
+        return launch_quad_r<Q, true, false>(a, v, c, colour, grid, s, ev);
     }
-    if (a.met_le) return launch_quad_r<Q, false, true>(a, colour, grid, s, ev);
-    return launch_quad_r<Q, false, false>(a, colour, grid, s, ev);
+    if (a.met_le) return launch_quad_r<Q, false, true>(a, v, c, colour, grid, s, ev);
+    return launch_quad_r<Q, false, false>(a, v, c, colour, grid, s, ev);
 }
 
-hipError_t launch_met_colour(const LatticeArgs& a, int colour, hipStream_t s, DispatchEvents ev)
+hipError_t launch_met_colour(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, hipStream_t s,
+                             DispatchEvents ev)
 {
     if (a.quad) {
-        const dim3 grid(((a.L + 3) / 4 + 63) / 64, a.row_blocks);
+        const dim3 grid(((a.L + 3) / 4 + 63) / 64, a.row_blocks + c.open);
         switch (a.q) {
-        case 2: return launch_quad<2>(a, colour, grid, s, ev);
-        case 3: return launch_quad<3>(a, colour, grid, s, ev);
-        case 4: return launch_quad<4>(a, colour, grid, s, ev);
-        case 5: return launch_quad<5>(a, colour, grid, s, ev);
-        default: return launch_quad<6>(a, colour, grid, s, ev);
+        case 2: return launch_quad<2>(a, v, c, colour, grid, s, ev);
+        case 3: return launch_quad<3>(a, v, c, colour, grid, s, ev);
+        case 4: return launch_quad<4>(a, v, c, colour, grid, s, ev);
+        case 5: return launch_quad<5>(a, v, c, colour, grid, s, ev);
+        default: return launch_quad<6>(a, v, c, colour, grid, s, ev);
         }
     }
-    const dim3 grid((a.L / 2 + 63) / 64, a.row_blocks), block(256);
+    const dim3 grid((a.L / 2 + 63) / 64, a.row_blocks + c.open), block(256);
     switch (a.q) {
-    case 2: return go(met_sweep_kernel<2>, grid, block, s, ev, a, colour);
-    case 3: return go(met_sweep_kernel<3>, grid, block, s, ev, a, colour);
-    case 4: return go(met_sweep_kernel<4>, grid, block, s, ev, a, colour);
-    case 5: return go(met_sweep_kernel<5>, grid, block, s, ev, a, colour);
-    default: return go(met_sweep_kernel<6>, grid, block, s, ev, a, colour);
+    case 2: return go(met_sweep_kernel<2>, grid, block, s, ev, a, v, c, colour);
+    case 3: return go(met_sweep_kernel<3>, grid, block, s, ev, a, v, c, colour);
+    case 4: return go(met_sweep_kernel<4>, grid, block, s, ev, a, v, c, colour);
+    case 5: return go(met_sweep_kernel<5>, grid, block, s, ev, a, v, c, colour);
+    default: return go(met_sweep_kernel<6>, grid, block, s, ev, a, v, c, colour);
     }
 }
 
@@ -407,15 +507,16 @@ hipError_t launch_set_stop(DevState* st, int64_t stop_at, hipStream_t s)
 }
 
 template <int Q>
-hipError_t launch_domain_q(const LatticeArgs& a, uint32_t pass, dim3 grid, uint32_t rows, hipStream_t s,
-                           const DispatchEvents& ev)
+hipError_t launch_domain_q(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t pass, dim3 grid, uint32_t rows,
+                           hipStream_t s, const DispatchEvents& ev)
 {
-    if (a.L % 4 == 0) return go(met_domain_kernel<Q, 2>, grid, dim3(256), s, ev, a, pass, rows);
-    if (a.L % 2 == 0) return go(met_domain_kernel<Q, 1>, grid, dim3(256), s, ev, a, pass, rows);
-    return go(met_domain_kernel<Q, 0>, grid, dim3(256), s, ev, a, pass, rows);
+    if (a.L % 4 == 0) return go(met_domain_kernel<Q, 2>, grid, dim3(256), s, ev, a, v, c, pass, rows);
+    if (a.L % 2 == 0) return go(met_domain_kernel<Q, 1>, grid, dim3(256), s, ev, a, v, c, pass, rows);
+    return go(met_domain_kernel<Q, 0>, grid, dim3(256), s, ev, a, v, c, pass, rows);
 }
 
-hipError_t launch_met_domain(const LatticeArgs& a, uint32_t pass, hipStream_t s, DispatchEvents ev)
+hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t pass, hipStream_t s,
+                             DispatchEvents ev)
 {
     // lanes own column quads (L % 4 == 0) or pairs, (L + 1) / 2 per row; rows
     // per wavefront for ~8192 wavefronts (measured at L = 4096 with pairs:
@@ -424,13 +525,13 @@ hipError_t launch_met_domain(const LatticeArgs& a, uint32_t pass, hipStream_t s,
     const uint32_t groups = (lanes + 63) / 64;
     const uint32_t wpg = groups >= 8192 ? 1 : 8192 / groups;
     const uint32_t rows = min(32u, (a.L + wpg - 1) / wpg);
-    const dim3 grid(groups, ((a.L + rows - 1) / rows + 3) / 4);
+    const dim3 grid(groups, ((a.L + rows - 1) / rows + 3) / 4 + c.open);
     switch (a.q) {
-    case 2: return launch_domain_q<2>(a, pass, grid, rows, s, ev);
-    case 3: return launch_domain_q<3>(a, pass, grid, rows, s, ev);
-    case 4: return launch_domain_q<4>(a, pass, grid, rows, s, ev);
-    case 5: return launch_domain_q<5>(a, pass, grid, rows, s, ev);
-    default: return launch_domain_q<6>(a, pass, grid, rows, s, ev);
+    case 2: return launch_domain_q<2>(a, v, c, pass, grid, rows, s, ev);
+    case 3: return launch_domain_q<3>(a, v, c, pass, grid, rows, s, ev);
+    case 4: return launch_domain_q<4>(a, v, c, pass, grid, rows, s, ev);
+    case 5: return launch_domain_q<5>(a, v, c, pass, grid, rows, s, ev);
+    default: return launch_domain_q<6>(a, v, c, pass, grid, rows, s, ev);
     }
 }
 
@@ -470,10 +571,10 @@ hipError_t launch_state_counts(const LatticeArgs& a, int64_t* out, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_sw_tiles(const LatticeArgs& a, hipStream_t s, DispatchEvents ev)
+hipError_t launch_sw_tiles(const LatticeArgs& a, const VolArgs& v, StepCtl c, hipStream_t s, DispatchEvents ev)
 {
     const dim3 grid((a.L + kTW - 1) / kTW, (a.L + kTH - 1) / kTH);
-    return go(sw_tile_kernel, grid, dim3(kTT), s, ev, a);
+    return go(sw_tile_kernel, grid, dim3(kTT), s, ev, a, v, c);
 }
 
 __global__ void sw_counters_init_kernel(uint32_t* ecnt, uint32_t n)
@@ -488,28 +589,32 @@ hipError_t launch_sw_counters_init(const LatticeArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// Workgroups that open the next step of `count` chains, one wavefront each.
+inline uint32_t open_blocks(uint32_t count, StepCtl c) { return c.open ? (count + 3) / 4 : 0; }
+
 template <int Q>
-void launch_batch_q(const BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total, int colour,
-                    int le, hipStream_t s)
+void launch_batch_q(BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total, int colour, int le,
+                    StepCtl c, hipStream_t s)
 {
+    const uint32_t grid = total + open_blocks(count, c);
     if (le) {
-        if (colour == 0) met_batch_kernel<Q, 0, true><<<total, 256, 0, s>>>(ent, start, count);
-        else met_batch_kernel<Q, 1, true><<<total, 256, 0, s>>>(ent, start, count);
+        if (colour == 0) met_batch_kernel<Q, 0, true><<<grid, 256, 0, s>>>(ent, start, count, total, c);
+        else met_batch_kernel<Q, 1, true><<<grid, 256, 0, s>>>(ent, start, count, total, c);
     } else {
-        if (colour == 0) met_batch_kernel<Q, 0, false><<<total, 256, 0, s>>>(ent, start, count);
-        else met_batch_kernel<Q, 1, false><<<total, 256, 0, s>>>(ent, start, count);
+        if (colour == 0) met_batch_kernel<Q, 0, false><<<grid, 256, 0, s>>>(ent, start, count, total, c);
+        else met_batch_kernel<Q, 1, false><<<grid, 256, 0, s>>>(ent, start, count, total, c);
     }
 }
 
-hipError_t launch_met_batch(const BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks,
-                            int q, int colour, int le, hipStream_t s)
+hipError_t launch_met_batch(BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks, int q,
+                            int colour, int le, StepCtl c, hipStream_t s)
 {
     switch (q) {
-    case 2: launch_batch_q<2>(ent, start, count, total_blocks, colour, le, s); break;
-    case 3: launch_batch_q<3>(ent, start, count, total_blocks, colour, le, s); break;
-    case 4: launch_batch_q<4>(ent, start, count, total_blocks, colour, le, s); break;
-    case 5: launch_batch_q<5>(ent, start, count, total_blocks, colour, le, s); break;
-    default: launch_batch_q<6>(ent, start, count, total_blocks, colour, le, s); break;
+    case 2: launch_batch_q<2>(ent, start, count, total_blocks, colour, le, c, s); break;
+    case 3: launch_batch_q<3>(ent, start, count, total_blocks, colour, le, c, s); break;
+    case 4: launch_batch_q<4>(ent, start, count, total_blocks, colour, le, c, s); break;
+    case 5: launch_batch_q<5>(ent, start, count, total_blocks, colour, le, c, s); break;
+    default: launch_batch_q<6>(ent, start, count, total_blocks, colour, le, c, s); break;
     }
     return hipGetLastError();
 }
@@ -520,19 +625,19 @@ hipError_t launch_volume_batch(BatchEntry* ent, uint32_t count, int mode, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_sw_batch(const BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks,
-                           int stage, hipStream_t s)
+hipError_t launch_sw_batch(BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total_blocks, int stage,
+                           StepCtl c, hipStream_t s)
 {
     if (total_blocks == 0) return hipSuccess;
-    if (stage == 0) sw_tile_batch_kernel<<<total_blocks, kTT, 0, s>>>(ent, start, count);
-    else sw_flip_batch_kernel<<<total_blocks, kTT, 0, s>>>(ent, start, count);
+    if (stage == 0) sw_tile_batch_kernel<<<total_blocks, kTT, 0, s>>>(ent, start, count, c);
+    else sw_flip_batch_kernel<<<total_blocks + open_blocks(count, c), kTT, 0, s>>>(ent, start, count, total_blocks, c);
     return hipGetLastError();
 }
 
-hipError_t launch_sw_flip_tiles(const LatticeArgs& a, hipStream_t s, DispatchEvents ev)
+hipError_t launch_sw_flip_tiles(const LatticeArgs& a, const VolArgs& v, StepCtl c, hipStream_t s, DispatchEvents ev)
 {
-    const dim3 grid((a.L + kTW - 1) / kTW, (a.L + kTH - 1) / kTH);
-    return go(sw_flip_tile_kernel, grid, dim3(kTT), s, ev, a);
+    const dim3 grid((a.L + kTW - 1) / kTW, (a.L + kTH - 1) / kTH + c.open);
+    return go(sw_flip_tile_kernel, grid, dim3(kTT), s, ev, a, v, c);
 }
 
 hipError_t launch_sw_labels(const LatticeArgs& a, uint32_t* out, hipStream_t s)

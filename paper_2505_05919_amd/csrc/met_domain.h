@@ -158,11 +158,20 @@ __device__ __forceinline__ uint32_t dom_rows_quad(const LatticeArgs& a, const ui
 
 // MODE 0: column pairs, odd L; 1: column pairs, L % 4 == 2; 2: quads, L % 4 == 0.
 template <int Q, int MODE>
-__global__ __launch_bounds__(256) void met_domain_kernel(LatticeArgs a, uint32_t pass, uint32_t rows)
+__global__ __launch_bounds__(256) void met_domain_kernel(LatticeArgs a, VolArgs va, StepCtl ctl, uint32_t pass,
+                                                         uint32_t rows)
 {
-    const int skip = a.st->skip, theta = a.st->theta;
-    const uint32_t t = a.st->t_cur;
+    if (ctl.open && blockIdx.y + 1 == gridDim.y) {
+        __shared__ double term[40];
+        if (blockIdx.x == 0 && threadIdx.x < 64) open_next(va, term, a.st->view + (ctl.bank ^ 1u));
+        return;
+    }
+    StepView* view = a.st->view + ctl.bank;
+    const int skip = view->skip;
+    int theta = pass == 0 ? view->theta : view->theta2;
+    const uint32_t t = view->t_cur;
     if (skip) return;                                      // step limit reached
+    if (pass == 0 && view->pending) theta = resolve_step(va, view, false, blockIdx.x + blockIdx.y == 0);
     __shared__ uint2 tbl[32];
     const uint32_t arm = __builtin_amdgcn_readfirstlane(domain_arm(a, t, pass));
     const uint32_t L = a.L;
@@ -183,5 +192,5 @@ __global__ __launch_bounds__(256) void met_domain_kernel(LatticeArgs a, uint32_t
         default: wsum = MODE == 2 ? dom_rows_quad<Q, 3>(a, tbl, t, j, y0, y1) : dom_rows<Q, EVEN, 3>(a, tbl, t, j, y0, y1); break;
         }
     }
-    met_reduce(wsum, a.slots, blockIdx.x + blockIdx.y * gridDim.x);
+    met_reduce(wsum, a.slots + (pass ? kBankSlots : 0), blockIdx.x + blockIdx.y * gridDim.x);
 }

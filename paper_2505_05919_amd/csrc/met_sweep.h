@@ -310,7 +310,7 @@ __device__ __forceinline__ void met_table(const LatticeArgs& a, uint2* tbl, int 
     __syncthreads();
 }
 
-__device__ __forceinline__ void met_reduce(uint32_t wsum, int64_t* slots, uint32_t slot)
+__device__ __forceinline__ void met_reduce(uint32_t wsum, int64_t* bank, uint32_t slot)
 {
     // unpack the per-lane sums: wsum = sum dc + 2^10 sum dh + 2^20 accepted.
     // Exact while the 10-bit fields hold the sums: a cell's four moves change
@@ -324,7 +324,7 @@ __device__ __forceinline__ void met_reduce(uint32_t wsum, int64_t* slots, uint32
     const int sdh = (r1v << 22) >> 22;
     const int nacc = (r1v - sdh) >> 10;
     const int v[3] = {sdh, sdc, nacc};
-    block_add<3>(v, slots + (slot & (kSlots - 1)), kSlots);
+    block_add<3>(v, bank + (slot & (kSlots - 1)), kSlots);
 }
 
 // The waves of a SIMD are issued oldest first, so with equal work the oldest
@@ -361,9 +361,14 @@ struct ProgressPrio {
 // are requested before the state (skip flag, theta, step) is read, and the
 // first wait covers all three at once.
 template <int Q, int KAPPA, bool R, bool LE>
-__global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a)
+__global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs va, StepCtl ctl)
 {
-    __shared__ uint2 tbl[64];
+    __shared__ __align__(16) uint2 tbl[64];
+    static_assert(sizeof(tbl) >= 40 * sizeof(double), "the shell terms of an opened step");
+    if (KAPPA == 1 && blockIdx.y == a.row_blocks) {
+        if (blockIdx.x == 0 && threadIdx.x < 64) open_next(va, (double*)tbl, a.st->view + (ctl.bank ^ 1u));
+        return;
+    }
     const uint32_t tid = threadIdx.x;
     uint2 e = make_uint2(0u, 0u);
     if (tid < 64) e = met_table_entry<LE>(a, (int)tid);
@@ -383,8 +388,11 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a)
     constexpr int PE = KAPPA, PO = 1 - KAPPA;
     QuadBytes cur = {};
     if (active) cur = met_load4<PE, R, false>(a, rs, y0, x4, x4h, xl, xr);
-    const int skip = a.st->skip, theta = a.st->theta;
-    const uint32_t t = a.st->t_cur;
+    StepView* view = a.st->view + ctl.bank;
+    const int skip = view->skip;
+    int theta = KAPPA == 0 ? view->theta : view->theta2;
+    const uint32_t t = view->t_cur;
+    if (KAPPA == 0 && view->pending) theta = resolve_step(va, view, false, blockIdx.x + blockIdx.y == 0);
     if (tid < 64) tbl[tid] = e;
     __syncthreads();
     if (skip) return;                                          // step limit reached (uniform)
@@ -401,7 +409,7 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a)
             met_quad<Q, PO, R, true, LE>(a, rs, tb, t, y + 1, x4, odd, wsum, ragged);
         }
     }
-    met_reduce(wsum, a.slots, blockIdx.x + blockIdx.y * gridDim.x);
+    met_reduce(wsum, a.slots + KAPPA * kBankSlots, blockIdx.x + blockIdx.y * gridDim.x);
 }
 
 // Byte-lane variant (any even L): lane i owns the column pair (2i, 2i+1).
@@ -444,16 +452,25 @@ __device__ __forceinline__ uint32_t met_byte_block(const LatticeArgs& a, uint2* 
 }
 
 template <int Q>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void met_sweep_kernel(LatticeArgs a, int colour)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void met_sweep_kernel(LatticeArgs a, VolArgs va, StepCtl ctl,
+                                                                                                             int colour)
 {
-    const int skip = a.st->skip, theta = a.st->theta;
-    const uint32_t t = a.st->t_cur;
+    if (blockIdx.y == a.row_blocks) {
+        __shared__ double term[40];
+        if (blockIdx.x == 0 && threadIdx.x < 64) open_next(va, term, a.st->view + (ctl.bank ^ 1u));
+        return;
+    }
+    StepView* view = a.st->view + ctl.bank;
+    const int skip = view->skip;
+    int theta = colour == 0 ? view->theta : view->theta2;
+    const uint32_t t = view->t_cur;
     if (skip) return;                                      // step limit reached
+    if (colour == 0 && view->pending) theta = resolve_step(va, view, false, blockIdx.x + blockIdx.y == 0);
     // 32 entries: indices d + 16 for d in -15..15, so that even out-of-range
     // bond indices (a caller-supplied configuration) cannot read outside it.
     __shared__ uint2 tbl[32];
     const uint32_t wsum = met_byte_block<Q, true>(a, tbl, t, theta, colour, blockIdx.x, blockIdx.y);
-    met_reduce(wsum, a.slots, blockIdx.x + blockIdx.y * gridDim.x);
+    met_reduce(wsum, a.slots + colour * kBankSlots, blockIdx.x + blockIdx.y * gridDim.x);
 }
 
 // The chain c of workgroup b in a batched launch: start[c] <= b < start[c + 1]
@@ -495,16 +512,25 @@ __device__ __forceinline__ uint32_t batch_chain(const uint32_t* start, uint32_t 
 // faster than the uncapped register budget.
 template <int Q, int KAPPA, bool LE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void met_batch_kernel(
-    const BatchEntry* __restrict__ ent, const uint32_t* __restrict__ start, uint32_t count)
+    BatchEntry* __restrict__ ent, const uint32_t* __restrict__ start, uint32_t count, uint32_t total, StepCtl ctl)
 {
     __shared__ uint2 tbl[32];
+    if (KAPPA == 1 && blockIdx.x >= total) {               // opens the next step of four chains
+        __shared__ double term[4][40];
+        const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = 4 * (blockIdx.x - total) + w;
+        if (c < count) open_next(ent[c].va, term[w], ent[c].view + (ctl.bank ^ 1u));
+        return;
+    }
     const uint32_t lo = batch_chain(start, count, blockIdx.x);
     const LatticeArgs a = ent[lo].la;
-    // the step state comes with the entry (written by the batched volume
-    // kernel), not through a second, dependent load from la.st
-    const int skip = ent[lo].skip, theta = ent[lo].theta;
-    const uint32_t t = ent[lo].t_cur;
+    // the step comes with the entry, not through a second, dependent load from
+    // la.st
+    StepView* view = ent[lo].view + ctl.bank;
+    const int skip = view->skip;
+    int theta = KAPPA == 0 ? view->theta : view->theta2;
+    const uint32_t t = view->t_cur;
     if (skip) return;                                      // step limit reached
+    if (KAPPA == 0 && view->pending) theta = resolve_step(ent[lo].va, view, false, blockIdx.x == start[lo]);
     const uint32_t units = ent[lo].units, upr = ent[lo].upr, K = ent[lo].iters;
     const double upr_inv = ent[lo].upr_inv;
     const uint32_t local = blockIdx.x - start[lo];
@@ -584,17 +610,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
             pr = prn;
         }
     }
-    met_reduce(wsum, a.slots, local);
+    met_reduce(wsum, a.slots + KAPPA * kBankSlots, local);
 }
 
-// One wavefront per chain: fold and open the next step of every chain
-// (mode kVolMet before a Metropolis sweep, kVolSw before an SW step).
+// One wavefront per chain: fold and open the first step of a call for every
+// chain (mode kVolMet before Metropolis sweeps, kVolSw before SW steps).
 __global__ __launch_bounds__(64) void volume_batch_kernel(BatchEntry* __restrict__ ent, int mode)
 {
     __shared__ double term[40];
-    VolArgs v = ent[blockIdx.x].va;
+    BatchEntry& e = ent[blockIdx.x];
+    VolArgs v = e.va;
     v.mode = mode;
     if (mode != kVolMet) v.met_att_add = 0;
-    volume_step(v, term, ent + blockIdx.x);
+    volume_step(v, term, mode == kVolMet ? e.view : v.st->view);
 }
-

@@ -37,11 +37,10 @@ struct SwBondCtx {
     bool cov_on;
 };
 
-__device__ __forceinline__ SwBondCtx sw_ctx(const LatticeArgs& a)
+__device__ __forceinline__ SwBondCtx sw_ctx(const LatticeArgs& a, uint32_t t, int theta)
 {
-    const int theta = a.st->theta;
     SwBondCtx k;
-    k.t = a.st->t_cur;
+    k.t = t;
     k.thr_s = a.tab->sw[0];
     k.thr_e = a.tab->sw[1 + theta];
     k.cov_on = theta == 1 && a.jeff_sign != 0;
@@ -141,12 +140,12 @@ __device__ __forceinline__ TileGeom tile_geom(uint32_t L, uint32_t bx, uint32_t 
 // tiles at L = 1414, against 2, 4, 16, 32 and 64).
 constexpr uint32_t kTileXcd = 8, kTileRun = 8;
 
-// The tile of this workgroup in a single-chain launch (grid = tiles), in the
+// The tile of this workgroup in a single-chain launch (gridDim.x x ncy tiles), in the
 // XCD-aware order; the last n % (8 kTileRun) tiles, which do not fill a run
 // on every XCD, keep their place.
-__device__ __forceinline__ TileGeom grid_tile(uint32_t L)
+__device__ __forceinline__ TileGeom grid_tile(uint32_t L, uint32_t ncy)
 {
-    const uint32_t ncx = gridDim.x, n = ncx * gridDim.y;
+    const uint32_t ncx = gridDim.x, n = ncx * ncy;
     const uint32_t b = blockIdx.x + blockIdx.y * ncx;
     uint32_t tile = b;
     if (b < n - n % (kTileXcd * kTileRun)) {
@@ -305,8 +304,8 @@ __device__ __forceinline__ void unite_global(uint32_t* label, uint32_t pu, uint3
 }
 
 // lut: 64 bytes, lab: 4 kTC words, act: kEdgeBytes bytes of LDS.
-__device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const TileGeom& g, uint8_t* lut, uint32_t* lab,
-                                             uint8_t* act)
+__device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const VolArgs& va, uint32_t bank, const TileGeom& g,
+                                             uint8_t* lut, uint32_t* lab, uint8_t* act)
 {
     // Waves of a SIMD issue oldest first; a workgroup that has finished its
     // bonds yields to those still computing theirs, so all tiles reach the
@@ -321,9 +320,12 @@ __device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const TileGeo
     const uint32_t x = g.x0 + lane;
     const uint32_t vx = col_in ? x : 0u, vxp = col_in ? ((x + 1 == L) ? 0u : x + 1) : 0u;
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(a.sigma, 4 * N), rm = buf_rsrc(a.mask, N);
-    if (a.st->skip) return;
+    StepView* view = a.st->view + bank;
+    if (view->skip) return;
+    int theta = view->theta;
+    if (view->pending) theta = resolve_step(va, view, true, g.id == 0);
     build_incell_lut(lut);
-    const SwBondCtx k = sw_ctx(a);
+    const SwBondCtx k = sw_ctx(a, view->t_cur, theta);
     uint32_t mk[kTC / kTT];
 #pragma unroll
     for (uint32_t i = 0; i < kTC / kTT; ++i) {
@@ -465,12 +467,12 @@ __device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const TileGeo
     }
 }
 
-__global__ __launch_bounds__(kTT) void sw_tile_kernel(LatticeArgs a)
+__global__ __launch_bounds__(kTT) void sw_tile_kernel(LatticeArgs a, VolArgs va, StepCtl ctl)
 {
     __shared__ uint8_t lut[64];
     __shared__ uint32_t lab[4 * kTC];
     __shared__ uint8_t act[kEdgeBytes];
-    sw_tile_body(a, grid_tile(a.L), lut, lab, act);
+    sw_tile_body(a, va, ctl.bank, grid_tile(a.L, gridDim.y), lut, lab, act);
 }
 
 // LDS of the flip: the compacted roots of the interior components, whose
@@ -503,7 +505,7 @@ __device__ __forceinline__ uint32_t wave_excl_scan5(uint32_t c, uint32_t& total)
     return pre;
 }
 
-__device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, const TileGeom& g, FlipLds& lds)
+__device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, uint32_t bank, const TileGeom& g, FlipLds& lds)
 {
     uint16_t* roots = lds.roots;
     uint8_t* sh = lds.sh;
@@ -535,9 +537,16 @@ __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, const TileGeo
         }
     }
     // the loads above do not depend on the chain state; read it now
-    if (a.st->skip) return;                   // step limit reached (uniform, before any barrier)
-    const uint32_t t = a.st->t_cur;
-    if (g.id == 0 && threadIdx.x == 0) a.st->sw_done = 1;
+    const StepView* view = a.st->view + bank;
+    if (view->skip) return;                   // step limit reached (uniform, before any barrier)
+    const uint32_t t = view->t_cur;
+    if (g.id == 0) {
+        if (threadIdx.x == 0) a.st->sw_done = 1;
+        // the other bank's recount, of the step before, is dead: the next step
+        // adds its own there
+        static_assert(kTT >= 2 * kSlots, "one thread per slot of the two recounted values");
+        if (threadIdx.x < 2 * kSlots) a.slots[(bank ^ 1u) * kBankSlots + threadIdx.x] = 0;
+    }
 #pragma unroll
     for (uint32_t i = 0; i < 4 * kTC / kTT; ++i) lds.osg[ent_local(wave, lane, i)] = (uint8_t)os[i];
     // the 16-bit local roots, two per register for the rest of the kernel
@@ -663,13 +672,19 @@ __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, const TileGeo
         }
     }
     const int v2[2] = {hb, co};
-    block_add<2, kTT>(v2, a.slots + (g.id & (kSlots - 1)), kSlots);
+    block_add<2, kTT>(v2, a.slots + bank * kBankSlots + (g.id & (kSlots - 1)), kSlots);
 }
 
-__global__ __launch_bounds__(kTT) __attribute__((amdgpu_waves_per_eu(8, 8))) void sw_flip_tile_kernel(LatticeArgs a)
+__global__ __launch_bounds__(kTT) __attribute__((amdgpu_waves_per_eu(8, 8))) void sw_flip_tile_kernel(LatticeArgs a, VolArgs va,
+                                                                                                    StepCtl ctl)
 {
-    __shared__ FlipLds lds;
-    sw_flip_body(a, grid_tile(a.L), lds);
+    __shared__ __align__(16) FlipLds lds;
+    const uint32_t ncy = gridDim.y - ctl.open;
+    if (blockIdx.y == ncy) {                  // opens the next step
+        if (blockIdx.x == 0 && threadIdx.x < 64) open_next(va, (double*)&lds, a.st->view + (ctl.bank ^ 1u));
+        return;
+    }
+    sw_flip_body(a, ctl.bank, grid_tile(a.L, ncy), lds);
 }
 
 // label[idx] = the minimum of idx's cluster, for every bond index; written
@@ -681,7 +696,7 @@ __global__ __launch_bounds__(kTT) void sw_labels_kernel(LatticeArgs a, uint32_t*
     __shared__ uint32_t lab[4 * kTC];
     build_incell_lut(lut);
     const uint32_t L = a.L, N = a.N;
-    const TileGeom g = grid_tile(L);
+    const TileGeom g = grid_tile(L, gridDim.y);
     uint32_t mk[kTC / kTT];
     tile_masks(a, g, mk);
     __syncthreads();
@@ -721,21 +736,32 @@ __device__ __forceinline__ TileGeom batch_tile(const LatticeArgs& a, uint32_t b,
 }
 
 __global__ __launch_bounds__(kTT) void sw_tile_batch_kernel(const BatchEntry* __restrict__ ent,
-                                                            const uint32_t* __restrict__ tstart, uint32_t count)
+                                                            const uint32_t* __restrict__ tstart, uint32_t count,
+                                                            StepCtl ctl)
 {
     __shared__ uint8_t lut[64];
     __shared__ uint32_t lab[4 * kTC];
     __shared__ uint8_t act[kEdgeBytes];
     const uint32_t c = batch_chain(tstart, count, blockIdx.x);
     const LatticeArgs a = ent[c].la;
-    sw_tile_body(a, batch_tile(a, blockIdx.x, tstart[c], tstart[c + 1]), lut, lab, act);
+    sw_tile_body(a, ent[c].va, ctl.bank, batch_tile(a, blockIdx.x, tstart[c], tstart[c + 1]), lut, lab, act);
 }
 
 __global__ __launch_bounds__(kTT) __attribute__((amdgpu_waves_per_eu(8, 8))) void sw_flip_batch_kernel(
-    const BatchEntry* __restrict__ ent, const uint32_t* __restrict__ tstart, uint32_t count)
+    const BatchEntry* __restrict__ ent, const uint32_t* __restrict__ tstart, uint32_t count, uint32_t total,
+    StepCtl ctl)
 {
-    __shared__ FlipLds lds;
+    __shared__ __align__(16) FlipLds lds;
+    if (blockIdx.x >= total) {                // opens the next step of four chains
+        const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = 4 * (blockIdx.x - total) + w;
+        if (i >= count) return;
+        VolArgs v = ent[i].va;
+        v.mode = kVolSw;
+        v.met_att_add = 0;
+        open_next(v, (double*)&lds + 40 * w, v.st->view + (ctl.bank ^ 1u));
+        return;
+    }
     const uint32_t c = batch_chain(tstart, count, blockIdx.x);
     const LatticeArgs a = ent[c].la;
-    sw_flip_body(a, batch_tile(a, blockIdx.x, tstart[c], tstart[c + 1]), lds);
+    sw_flip_body(a, ctl.bank, batch_tile(a, blockIdx.x, tstart[c], tstart[c + 1]), lds);
 }
