@@ -598,11 +598,11 @@ void launch_batch_q(BatchEntry* ent, const uint32_t* start, uint32_t count, uint
 {
     const uint32_t grid = total + open_blocks(count, c);
     if (le) {
-        if (colour == 0) met_batch_kernel<Q, 0, true><<<grid, 256, 0, s>>>(ent, start, count, total, c);
-        else met_batch_kernel<Q, 1, true><<<grid, 256, 0, s>>>(ent, start, count, total, c);
+        if (colour == 0) met_batch_kernel<Q, 0, true><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
+        else met_batch_kernel<Q, 1, true><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
     } else {
-        if (colour == 0) met_batch_kernel<Q, 0, false><<<grid, 256, 0, s>>>(ent, start, count, total, c);
-        else met_batch_kernel<Q, 1, false><<<grid, 256, 0, s>>>(ent, start, count, total, c);
+        if (colour == 0) met_batch_kernel<Q, 0, false><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
+        else met_batch_kernel<Q, 1, false><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
     }
 }
 

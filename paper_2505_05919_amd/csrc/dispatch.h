@@ -11,6 +11,19 @@
 
 namespace cvf {
 
+// Cache policy of the stores that leave a launch's results in memory (the
+// builtins' cache-policy bits sc0 | sc1): written through L2 as they are made.
+// A launch ends by writing its dirty L2 lines back, up to 32 MB in the eight
+// XCDs' caches, with the chip otherwise idle; written through, that traffic
+// runs beside the launch's arithmetic instead.  Measured: Metropolis sweeps at
+// L = 2048 / 4096 28.3 / 76.8 -> 25.0 / 74.2 us, a Swendsen-Wang step at
+// L = 1414 45.3 -> 42.8 us, cubic passes at 260^3 152.8 -> 151.0 us (sc1 alone
+// the same, nt no change).  Single bytes per lane (column pairs, odd rows,
+// bond masks) and the cubic shifts stay plain stores: written through, batches of
+// column-pair lattices went from 58 to 60 us and the cubic step from 126.0 to
+// 127.4.
+constexpr int kThrough = 17;
+
 // Null events: a plain launch.
 struct DispatchEvents {
     hipEvent_t start = nullptr;

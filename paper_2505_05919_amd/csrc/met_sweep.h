@@ -149,12 +149,12 @@ __device__ __forceinline__ uint32_t ld32(__amdgpu_buffer_rsrc_t r, uint32_t voff
 
 __device__ __forceinline__ void st32(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)voff, (int)soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)voff, (int)soff, kThrough);
 }
 
 __device__ __forceinline__ void st16(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, kThrough);
 }
 
 // Dword of a row that starts two bytes past a dword boundary (MIS): two
@@ -512,25 +512,30 @@ __device__ __forceinline__ uint32_t batch_chain(const uint32_t* start, uint32_t 
 // faster than the uncapped register budget.
 template <int Q, int KAPPA, bool LE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void met_batch_kernel(
-    BatchEntry* __restrict__ ent, const uint32_t* __restrict__ start, uint32_t count, uint32_t total, StepCtl ctl)
+    const BatchEntry* __restrict__ ent, BatchEntry* wr, const uint32_t* __restrict__ start, uint32_t count,
+    uint32_t total, StepCtl ctl)
 {
+    // wr: the entries again, for the views written here (the other bank's, or
+    // theta2 of a pending step, which this launch does not read); the entry
+    // itself is read through ent, with scalar loads
     __shared__ uint2 tbl[32];
     if (KAPPA == 1 && blockIdx.x >= total) {               // opens the next step of four chains
         __shared__ double term[4][40];
         const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = 4 * (blockIdx.x - total) + w;
-        if (c < count) open_next(ent[c].va, term[w], ent[c].view + (ctl.bank ^ 1u));
+        if (c < count) open_next(ent[c].va, term[w], wr[c].view + (ctl.bank ^ 1u));
         return;
     }
     const uint32_t lo = batch_chain(start, count, blockIdx.x);
     const LatticeArgs a = ent[lo].la;
     // the step comes with the entry, not through a second, dependent load from
     // la.st
-    StepView* view = ent[lo].view + ctl.bank;
+    const StepView* view = ent[lo].view + ctl.bank;
     const int skip = view->skip;
     int theta = KAPPA == 0 ? view->theta : view->theta2;
     const uint32_t t = view->t_cur;
     if (skip) return;                                      // step limit reached
-    if (KAPPA == 0 && view->pending) theta = resolve_step(ent[lo].va, view, false, blockIdx.x == start[lo]);
+    if (KAPPA == 0 && view->pending)
+        theta = resolve_step(ent[lo].va, wr[lo].view + ctl.bank, false, blockIdx.x == start[lo]);
     const uint32_t units = ent[lo].units, upr = ent[lo].upr, K = ent[lo].iters;
     const double upr_inv = ent[lo].upr_inv;
     const uint32_t local = blockIdx.x - start[lo];

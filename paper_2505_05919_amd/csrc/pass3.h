@@ -193,10 +193,10 @@ __device__ __forceinline__ void pass_move(const Lat3& a, const uint32_t* tab, co
     if (out != oldw) {
         const __amdgpu_buffer_rsrc_t r = plane_rsrc(a.sigma + (size_t)A * a.N, a.N);
         if (W) {
-            __builtin_amdgcn_raw_buffer_store_b32(out, r, (int)q.c, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(out, r, (int)q.c, 0, cvf::kThrough);
         } else {
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)out, r, (int)q.c, 0, 0);
-            if (q.n > 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(out >> 16), r, (int)q.c + 2, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)out, r, (int)q.c, 0, cvf::kThrough);
+            if (q.n > 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(out >> 16), r, (int)q.c + 2, 0, cvf::kThrough);
         }
     }
 }

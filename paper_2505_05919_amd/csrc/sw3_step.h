@@ -243,6 +243,13 @@ __device__ __forceinline__ uint32_t get_cells(const uint8_t* p, uint32_t c, uint
     return n > 2 ? lo | ((uint32_t)*(const uint16_t*)(p + c + 2) << 16) : lo;
 }
 
+// A store written through L2 (see kThrough).
+template <class V>
+__device__ __forceinline__ void put_through(V* p, V v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 template <uint32_t C>
 __device__ __forceinline__ void put_cells(uint8_t* p, uint32_t c, uint32_t n, bool whole, uint32_t v)
 {
@@ -510,7 +517,7 @@ __global__ __launch_bounds__(TL::TT) void sw3_tile_kernel(Lat3 a, TileGrid3 tg)
             if (C == 1) {
                 *dst = (uint16_t)o[0];
             } else if (q.whole) {
-                *(uint2*)dst = make_uint2(o[0], o[C / 4]);
+                put_through((uint64_t*)dst, o[0] | ((uint64_t)o[C / 4] << 32));
             } else {
                 *(uint32_t*)dst = o[0];
                 if (q.n > 2) *(uint32_t*)(dst + 2) = o[C / 4];

@@ -383,7 +383,8 @@ __device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const VolArgs
             const uint32_t p = 2 * h + (j >> 2), ly = ent_row(wave, j & 3);
             if (ly < g.h && col_in) {
                 const __amdgpu_buffer_rsrc_t rl = buf_rsrc(a.lroot + (size_t)p * N, 2 * N);
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)e[j], rl, (int)voff, (int)(2 * (g.y0 + ly) * L), 0);
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)e[j], rl, (int)voff, (int)(2 * (g.y0 + ly) * L),
+                                                      kThrough);
                 const uint32_t v = p * kTC + ly * kTW + lane;
                 if (r[j] == v && (e[j] & kBorder)) {
                     // a root other tiles' unions may reach this step: written
@@ -650,7 +651,8 @@ __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, uint32_t bank
         uint32_t s = lds.osg[ent_local(wave, lane, i)] + sh[LR(i) & kIdx];
         s = s >= q ? s - q : s;
         if (col_in && ly < g.h)
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)s, rs, (int)voff, (int)((i >> 2) * N + (g.y0 + ly) * L), 0);
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)s, rs, (int)voff, (int)((i >> 2) * N + (g.y0 + ly) * L),
+                                                 kThrough);
         lds.osg[ent_local(wave, lane, i)] = (uint8_t)s;
     }
     __syncthreads();                          // the root list is dead: its space holds the new sigma
