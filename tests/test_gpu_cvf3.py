@@ -119,6 +119,16 @@ def test_cvf3_pass_groups(c3, oracle_mod, L, q, n):
     run3(c3, oracle_mod, op, [1, n] if n > 1 else [1])
 
 
+@pytest.mark.parametrize("L", [4, 8, 24, 44, 100])
+def test_cvf3_eta_pairs(c3, oracle_mod, L):
+    """The two-cube eta kernel over one workgroup up to runs of workgroups that
+    do not fill their last chunk, odd cubes wrapping along every axis, liquid
+    and gas (every proposal accepted)."""
+    for v0 in (1.2, 2.6):
+        op = oracle_mod.params_from_si(240.0, 0.1, L=L, seed=320 + L, v_init=v0)
+        run3(c3, oracle_mod, op, [1, 2])
+
+
 @pytest.mark.parametrize("L", [1288, 1290])
 def test_cvf3_max_size(c3, oracle_mod, L):
     """The largest lattices (N = L^3 < 2^31; 1288 runs the quad pass and the
