@@ -34,6 +34,7 @@
 namespace {
 
 #include "philox.h"
+#include "wave.h"
 
 constexpr uint32_t kInit = 0, kVol = 1, kSwb = 3, kSwf = 4, kOrd = 5, kDom = 6, kEta = 7;
 constexpr int kSlots = 256;              // counter slots, spread to avoid one hot atomic
@@ -94,12 +95,6 @@ __device__ __forceinline__ uint32_t udiv(uint32_t n, uint32_t d, double inv)
     return q;
 }
 
-__device__ __forceinline__ int wave_sum(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // U_LJ per molecule on the cubic lattice (Sec. II.A): shells m = |n|^2 in
 // ascending order, (distance/r0)^6 = v^2 m^3, cutoff 6^6.

@@ -43,8 +43,9 @@ namespace {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Rows per lane of a batched Metropolis pass before the autotuner runs.
-constexpr uint32_t kBatchDefaultRows = 4;
+// Rows per lane of a batched Metropolis pass before the autotuner runs (256
+// replicas of L 64..512: 2 / 4 / 6 / 8 rows 90 / 100 / 98 / 101 us per sweep).
+constexpr uint32_t kBatchDefaultRows = 2;
 
 int validate(const cvf_params* p)
 {
@@ -240,8 +241,9 @@ void chain_setup(const cvf_params* p, uint8_t* d_sigma, char* work, size_t work_
     {
         const MetShape m = met_shape(a.L);
         a.quad = m.quad;
-        a.rows = m.rows;
-        a.row_blocks = m.row_blocks;
+        const bool one = met_one_row(a.L, m);
+        a.rows = one ? 1 : m.rows;
+        a.row_blocks = one ? (a.L + 3) / 4 : m.row_blocks;
     }
     a.met_le = 1;                        // every threshold >= 1: acceptance is word <= thr - 1
     for (int th = 0; th < 2; ++th)
@@ -530,22 +532,18 @@ int batch_upload(cvf_batch* b, hipStream_t s, uint8_t* staging)
         BatchEntry& e = b->host[c];
         memset(&e, 0, sizeof(e));
         e.la = st->la;
-        // batched passes: quads for L % 4 == 0, column pairs for L % 4 == 2
-        // (no ragged quads: their body raises the register need of the
-        // batched kernel past its 8-wavefront budget)
-        e.la.quad = (e.la.L % 4 == 0) ? 1u : 0u;
+        // batched passes move quads, two-cell ones at the row ends of L % 4 == 2
+        e.la.quad = (e.la.L % 4 == 0) ? 1u : 2u;
         e.va = st->va;
         e.va.mode = kVolMet;
         e.va.met_att_add = 4 * (int64_t)st->N;
         const uint32_t Lc = e.la.L;
-        e.upr = e.la.quad ? Lc / 4 : Lc / 2;
+        e.upr = (Lc + 3) / 4;
         e.upr_inv = 1.0 / (double)e.upr;
         e.units = e.upr * (Lc / 2);
-        // the tuned parameter: a quad lane moves `rows` rows (rows / 2 units of
-        // two rows, 8 rows updates); a column-pair lane makes as many updates
-        // with twice the units, so that every full workgroup has the same work
+        // the tuned parameter: a lane moves `rows` rows (rows / 2 units of two rows)
         const uint32_t rows = b->rows > 0 ? (uint32_t)b->rows : kBatchDefaultRows;
-        e.iters = e.la.quad ? (rows / 2 < 1 ? 1 : rows / 2) : rows;
+        e.iters = rows / 2 < 1 ? 1 : rows / 2;
         e.blocks = (uint32_t)(((uint64_t)e.units + 256ull * e.iters - 1) / (256ull * e.iters));
         b->start[c] = total;
         total += e.blocks;

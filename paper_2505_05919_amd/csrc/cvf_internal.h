@@ -144,7 +144,7 @@ struct LatticeArgs {
     int32_t jeff_sign;       // sign of J_eff = J - P v_HB
     double met_invd;         // 1 / floor(2^32/(q-1))
     double flip_invd;        // 1 / floor(2^32/q)
-    uint32_t rows;           // Metropolis: rows per wavefront (even, <= 32)
+    uint32_t rows;           // Metropolis: rows per wavefront (1, or even, <= 32)
     uint32_t row_blocks;     // Metropolis: grid.y
     uint32_t quad;           // Metropolis: 1 / 2 = dword (4-column) lanes, L % 4 == 0 / 2; 0 = column pairs
     uint32_t met_le;         // 1: no Metropolis threshold is 0, so acceptance is one compare (word <= thr - 1)
@@ -170,13 +170,13 @@ struct VolArgs {
 enum VolMode { kVolMet = 0, kVolSw = 1, kVolFold = 2 };
 
 // One chain of a batch: its launch arguments and the work units of a
-// batched Metropolis colour pass (row pair x column quad, or x column pair
-// for L % 4 == 2), `iters` units per lane, `blocks` workgroups.
+// batched Metropolis colour pass (row pair x column quad), `iters` units per
+// lane, `blocks` workgroups.
 struct BatchEntry {
     LatticeArgs la;
     VolArgs va;
     uint32_t units;          // units per colour pass: (L / 2) * upr
-    uint32_t upr;            // units per row pair: L / 4 quads, or L / 2 column pairs
+    uint32_t upr;            // units per row pair: (L + 3) / 4 quads
     double upr_inv;          // 1 / upr
     uint32_t iters;          // units per lane
     uint32_t blocks;         // workgroups of this chain: ceil(units / (256 iters))

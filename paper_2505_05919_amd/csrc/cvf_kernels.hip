@@ -7,6 +7,7 @@
 #include "cvf_internal.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace cvf {
 
@@ -23,6 +24,7 @@ constexpr int kBlock = 256;           // 4 wavefronts of 64
 constexpr int kMaxBlocks = 8192;      // 256 CUs x 8 waves/SIMD x 4 SIMDs / 4 waves
 
 #include "philox.h"
+#include "wave.h"
 
 // floor(j / d) and j mod d for j < 2^32, d < 2^15: one FP64 multiply by the
 // reciprocal is at most one too small, never too large; one correction.
@@ -38,12 +40,6 @@ __device__ __forceinline__ uint32_t divmod(uint32_t j, uint32_t d, double inv, u
     return qt;
 }
 
-__device__ __forceinline__ int wave_sum(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 __device__ __forceinline__ int64_t wave_sum64(int64_t v)
 {

@@ -55,4 +55,14 @@ inline MetShape met_shape(uint32_t L)
     return met_shape_mode(L, quad);
 }
 
+// Largest side whose quads are moved one row per wavefront instead of by the
+// shape above: up to there the launch is bound by a wavefront's latency, not
+// by issue (us per sweep, one row / shape above: L = 256 8.9 / 10.3, L = 1024
+// 11.5 / 13.2, L = 1536 16.7 / 20.5, L = 2048 24.5 / 24.3,
+// L = 4096 79.1 / 72.9).
+#ifndef CVF_MET_ONE_ROW_MAX
+#define CVF_MET_ONE_ROW_MAX 2046
+#endif
+inline bool met_one_row(uint32_t L, const MetShape& m) { return m.quad != 0 && L <= CVF_MET_ONE_ROW_MAX; }
+
 }  // namespace cvf

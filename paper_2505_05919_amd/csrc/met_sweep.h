@@ -72,9 +72,9 @@ struct CellBytes {
     uint32_t s0, s1, s2, s3, f0, f1, f2, f3;
 };
 
-// Loads for the cell at column x of row y.  Row offsets go into the
-// wave-uniform scalar offset when y is the same for the whole wavefront, or
-// (VROW) into the per-lane offset when every lane has a row of its own.
+// Row offsets go into the wave-uniform scalar offset when y is the same for the
+// whole wavefront, or (VROW) into the per-lane offset when every lane has a row
+// of its own.
 template <bool VROW>
 struct RowSplit {
     // per-lane part and scalar part of the offset of column x in the row at o
@@ -82,32 +82,29 @@ struct RowSplit {
     __device__ __forceinline__ static uint32_t s(uint32_t base, uint32_t o) { return VROW ? base : base + o; }
 };
 
-template <bool VROW = false>
 __device__ __forceinline__ CellBytes met_load(const LatticeArgs& a, __amdgpu_buffer_rsrc_t rs, uint32_t y,
                                               uint32_t x, uint32_t xp, uint32_t xm)
 {
-    using RS = RowSplit<VROW>;
     const uint32_t L = a.L, N = a.N;
     const uint32_t yp = (y + 1 == L) ? 0 : y + 1, ym = (y == 0) ? L - 1 : y - 1;
     const uint32_t o0 = y * L, op = yp * L, om = ym * L;
     CellBytes b;
-    b.s0 = ld8(rs, RS::v(x, o0), RS::s(0, o0));
-    b.s1 = ld8(rs, RS::v(x, o0), RS::s(N, o0));
-    b.s2 = ld8(rs, RS::v(x, o0), RS::s(2 * N, o0));
-    b.s3 = ld8(rs, RS::v(x, o0), RS::s(3 * N, o0));
-    b.f0 = ld8(rs, RS::v(xp, o0), RS::s(N, o0));          // arm 1 of the +x neighbour
-    b.f1 = ld8(rs, RS::v(xm, o0), RS::s(0, o0));          // arm 0 of the -x neighbour
-    b.f2 = ld8(rs, RS::v(x, op), RS::s(3 * N, op));       // arm 3 of the +y neighbour
-    b.f3 = ld8(rs, RS::v(x, om), RS::s(2 * N, om));       // arm 2 of the -y neighbour
+    b.s0 = ld8(rs, x, o0);
+    b.s1 = ld8(rs, x, N + o0);
+    b.s2 = ld8(rs, x, 2 * N + o0);
+    b.s3 = ld8(rs, x, 3 * N + o0);
+    b.f0 = ld8(rs, xp, N + o0);              // arm 1 of the +x neighbour
+    b.f1 = ld8(rs, xm, o0);                  // arm 0 of the -x neighbour
+    b.f2 = ld8(rs, x, 3 * N + op);           // arm 3 of the +y neighbour
+    b.f3 = ld8(rs, x, 2 * N + om);           // arm 2 of the -y neighbour
     return b;
 }
 
 // Update the four arms of the cell (x, y) from its loaded bytes and store them.
-template <int Q, bool VROW = false, bool LE = false>
+template <int Q>
 __device__ __forceinline__ void met_cell(const LatticeArgs& a, __amdgpu_buffer_rsrc_t rs, const uint2* tbl,
                                          uint32_t t, uint32_t y, uint32_t x, const CellBytes& b, uint32_t& wsum)
 {
-    using RS = RowSplit<VROW>;
     const uint32_t N = a.N, o0 = y * a.L;
     uint32_t s0 = b.s0 << 2, s1 = b.s1 << 2, s2 = b.s2 << 2, s3 = b.s3 << 2;
     const uint32_t f0 = b.f0 << 2, f1 = b.f1 << 2, f2 = b.f2 << 2, f3 = b.f3 << 2;
@@ -115,15 +112,15 @@ __device__ __forceinline__ void met_cell(const LatticeArgs& a, __amdgpu_buffer_r
     const uint4 wa = philox(c, t, 0u, kStreamMet, a.key0, a.key1);
     const uint4 wb = philox(c, t, 1u, kStreamMet, a.key0, a.key1);
     const uint32_t p23 = (1u << s2) + (1u << s3);
-    met_arm<Q, LE>(s0, p23 + (1u << s1) + (8u << f0), wa.x, wa.y, tbl, wsum);
-    met_arm<Q, LE>(s1, p23 + (1u << s0) + (8u << f1), wa.z, wa.w, tbl, wsum);
+    met_arm<Q>(s0, p23 + (1u << s1) + (8u << f0), wa.x, wa.y, tbl, wsum);
+    met_arm<Q>(s1, p23 + (1u << s0) + (8u << f1), wa.z, wa.w, tbl, wsum);
     const uint32_t p01 = (1u << s0) + (1u << s1);
-    met_arm<Q, LE>(s2, p01 + (1u << s3) + (8u << f2), wb.x, wb.y, tbl, wsum);
-    met_arm<Q, LE>(s3, p01 + (1u << s2) + (8u << f3), wb.z, wb.w, tbl, wsum);
-    st8(rs, s0 >> 2, RS::v(x, o0), RS::s(0, o0));
-    st8(rs, s1 >> 2, RS::v(x, o0), RS::s(N, o0));
-    st8(rs, s2 >> 2, RS::v(x, o0), RS::s(2 * N, o0));
-    st8(rs, s3 >> 2, RS::v(x, o0), RS::s(3 * N, o0));
+    met_arm<Q>(s2, p01 + (1u << s3) + (8u << f2), wb.x, wb.y, tbl, wsum);
+    met_arm<Q>(s3, p01 + (1u << s2) + (8u << f3), wb.z, wb.w, tbl, wsum);
+    st8(rs, s0 >> 2, x, o0);
+    st8(rs, s1 >> 2, x, N + o0);
+    st8(rs, s2 >> 2, x, 2 * N + o0);
+    st8(rs, s3 >> 2, x, 3 * N + o0);
 }
 
 // ---------------------------------------------------------------------------
@@ -134,13 +131,12 @@ __device__ __forceinline__ void met_cell(const LatticeArgs& a, __amdgpu_buffer_r
 // for P = 0, right of it for P = 1).  The two bytes of the other colour are
 // written back unchanged -- nothing writes them during this pass.  Per row
 // and lane: 6 dword loads + 1 byte load + 4 dword stores for 2 cells.
-// R (L % 4 == 2): plane offsets stay dword-aligned, even rows start on a
-// dword and odd rows two bytes past one, so the dwords of odd rows are moved
-// as two 16-bit halves.  The last quad of a row holds columns L-2, L-1 and
-// two phantom bytes (the next row's first columns, or in odd rows a second
-// copy of the low half): only its first cell is real, its +x neighbour for
-// P = 1 is the wrapped edge byte, the phantom cell's counter increments are
-// dropped, and only the low half is stored.
+// R (L % 4 == 2): odd rows start two bytes past a dword boundary, which the
+// buffer operations take.  The last quad of a row holds columns L-2, L-1 and
+// two phantom bytes that are neither loaded nor stored: only its first cell is
+// real, its +x neighbour for P = 1 is the wrapped edge byte, and the phantom
+// cell's counter increments are dropped.  (Moving those rows as two 16-bit
+// halves took 18.7 / 29.9 us per sweep at L = 1414 / 2046, this 17.6 / 26.5.)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t ld32(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
@@ -157,34 +153,21 @@ __device__ __forceinline__ void st16(__amdgpu_buffer_rsrc_t r, uint32_t v, uint3
     __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, kThrough);
 }
 
-// Dword of a row that starts two bytes past a dword boundary (MIS): two
-// 16-bit halves, the high one at voff_hi (voff + 2; voff for the last quad
-// of a row, whose high half is a phantom, so that no load leaves sigma).
-template <bool MIS>
+// Dword of a quad in a row that may start two bytes past a dword boundary: the
+// buffer operations take any byte offset.  R: the last quad of a row (voff_hi
+// == voff) has only its low half, so that no load leaves sigma.
+template <bool R>
 __device__ __forceinline__ uint32_t ld32r(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t voff_hi, uint32_t soff)
 {
-    if (!MIS) return ld32(r, voff, soff);
-    const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
-    const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(r, (int)voff_hi, (int)soff, 0);
-    return lo | (hi << 16);
+    if (!R || voff_hi != voff) return ld32(r, voff, soff);
+    return __builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
 }
 
-// Store of a quad dword: whole, or (R) the low half only for the last quad
-// of a row, and as two halves in rows that start off a dword boundary.
-template <bool R, bool MIS>
-__device__ __forceinline__ void st32r(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff, uint32_t soff,
-                                      bool ragged)
+template <bool R>
+__device__ __forceinline__ void st32r(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff, uint32_t soff, bool ragged)
 {
-    if (!R) {
-        st32(r, v, voff, soff);
-    } else if (MIS) {
-        st16(r, v, voff, soff);
-        if (!ragged) st16(r, v >> 16, voff + 2, soff);
-    } else if (ragged) {
-        st16(r, v, voff, soff);
-    } else {
-        st32(r, v, voff, soff);
-    }
+    if (!R || !ragged) st32(r, v, voff, soff);
+    else st16(r, v, voff, soff);
 }
 
 struct QuadBytes {
@@ -193,26 +176,22 @@ struct QuadBytes {
     uint32_t edge;             // P=0: arm 0 of the column left of the quad; P=1: arm 1 right of it
 };
 
-// ODD: y is odd.  With R the row of y is off a dword boundary when y is odd,
-// and its neighbour rows (y +- 1, wrapping to 0 or L-1) when y is even.
-// VROW: row offsets per lane (see met_load; not combined with R).
-template <int P, bool R, bool ODD, bool VROW = false>
+// VROW: row offsets per lane (see RowSplit).
+template <int P, bool R, bool VROW = false>
 __device__ __forceinline__ QuadBytes met_load4(const LatticeArgs& a, __amdgpu_buffer_rsrc_t rs, uint32_t y,
                                                uint32_t x4, uint32_t x4h, uint32_t xl, uint32_t xr)
 {
-    static_assert(!(R && VROW), "ragged quads keep wave-uniform rows");
     using RS = RowSplit<VROW>;
-    constexpr bool DMIS = R && ODD, NMIS = R && !ODD;
     const uint32_t L = a.L, N = a.N;
     const uint32_t yp = (y + 1 == L) ? 0 : y + 1, ym = (y == 0) ? L - 1 : y - 1;
     const uint32_t o0 = y * L, op = yp * L, om = ym * L;
     QuadBytes q;
-    q.d0 = ld32r<DMIS>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(0, o0));
-    q.d1 = ld32r<DMIS>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(N, o0));
-    q.d2 = ld32r<DMIS>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(2 * N, o0));
-    q.d3 = ld32r<DMIS>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(3 * N, o0));
-    q.up3 = ld32r<NMIS>(rs, RS::v(x4, op), RS::v(x4h, op), RS::s(3 * N, op));
-    q.dn2 = ld32r<NMIS>(rs, RS::v(x4, om), RS::v(x4h, om), RS::s(2 * N, om));
+    q.d0 = ld32r<R>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(0, o0));
+    q.d1 = ld32r<R>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(N, o0));
+    q.d2 = ld32r<R>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(2 * N, o0));
+    q.d3 = ld32r<R>(rs, RS::v(x4, o0), RS::v(x4h, o0), RS::s(3 * N, o0));
+    q.up3 = ld32r<R>(rs, RS::v(x4, op), RS::v(x4h, op), RS::s(3 * N, op));
+    q.dn2 = ld32r<R>(rs, RS::v(x4, om), RS::v(x4h, om), RS::s(2 * N, om));
     q.edge = (P == 0) ? ld8(rs, RS::v(xl, o0), RS::s(0, o0)) : ld8(rs, RS::v(xr, o0), RS::s(N, o0));
     return q;
 }
@@ -233,7 +212,7 @@ __device__ __forceinline__ uint32_t put2(uint32_t d, uint32_t v1, uint32_t v2)
     return (d & keep) | w1 | (v2 << (8 * B2 - 2));
 }
 
-template <int Q, int P, bool R, bool ODD, bool LE = false, bool VROW = false>
+template <int Q, int P, bool R, bool LE = false, bool VROW = false>
 __device__ __forceinline__ void met_quad(const LatticeArgs& a, __amdgpu_buffer_rsrc_t rs, const uint2* tbl,
                                          uint32_t t, uint32_t y, uint32_t x4, const QuadBytes& q, uint32_t& wsum,
                                          bool ragged)
@@ -276,13 +255,12 @@ __device__ __forceinline__ void met_quad(const LatticeArgs& a, __amdgpu_buffer_r
         met_arm<Q, LE>(b3, p01 + (1u << b2) + (8u << f3), wb.z, wb.w, tbl, wsum);
     }
     if (R && ragged) wsum = wkeep;
-    constexpr bool DMIS = R && ODD;
     using RS = RowSplit<VROW>;
     const uint32_t xv = RS::v(x4, o0);
-    st32r<R, DMIS>(rs, put2<B1, B2>(q.d0, a0, b0), xv, RS::s(0, o0), ragged);
-    st32r<R, DMIS>(rs, put2<B1, B2>(q.d1, a1, b1), xv, RS::s(N, o0), ragged);
-    st32r<R, DMIS>(rs, put2<B1, B2>(q.d2, a2, b2), xv, RS::s(2 * N, o0), ragged);
-    st32r<R, DMIS>(rs, put2<B1, B2>(q.d3, a3, b3), xv, RS::s(3 * N, o0), ragged);
+    st32r<R>(rs, put2<B1, B2>(q.d0, a0, b0), xv, RS::s(0, o0), ragged);
+    st32r<R>(rs, put2<B1, B2>(q.d1, a1, b1), xv, RS::s(N, o0), ragged);
+    st32r<R>(rs, put2<B1, B2>(q.d2, a2, b2), xv, RS::s(2 * N, o0), ragged);
+    st32r<R>(rs, put2<B1, B2>(q.d3, a3, b3), xv, RS::s(3 * N, o0), ragged);
 }
 
 // Entry i (0..63) of the two-theta table: theta = i / 32, index d + 16 with
@@ -376,7 +354,7 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs 
     const uint32_t lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t j = blockIdx.x * 64 + lane;
-    const uint32_t y0 = (blockIdx.y * 4 + wave) * a.rows;      // even
+    const uint32_t y0 = (blockIdx.y * 4 + wave) * a.rows;      // even, or any row for rows = 1
     const bool active = j < ((L + 3) >> 2) && y0 < L;           // (L + 2) / 4 quads when R
     const uint32_t x4 = 4 * j;
     const bool ragged = R && x4 + 2 == L;
@@ -387,7 +365,11 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs 
     // even rows: updated cells at bytes KAPPA, KAPPA+2; odd rows: 1-KAPPA, 3-KAPPA
     constexpr int PE = KAPPA, PO = 1 - KAPPA;
     QuadBytes cur = {};
-    if (active) cur = met_load4<PE, R, false>(a, rs, y0, x4, x4h, xl, xr);
+    const bool one = a.rows == 1;                              // a row per wavefront: y0 may be odd
+    if (active) {
+        if (one && (y0 & 1)) cur = met_load4<PO, R>(a, rs, y0, x4, x4h, xl, xr);
+        else cur = met_load4<PE, R>(a, rs, y0, x4, x4h, xl, xr);
+    }
     StepView* view = a.st->view + ctl.bank;
     const int skip = view->skip;
     int theta = KAPPA == 0 ? view->theta : view->theta2;
@@ -398,15 +380,20 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs 
     if (skip) return;                                          // step limit reached (uniform)
     const uint2* tb = tbl + (theta ? 32 : 0);
     uint32_t wsum = 0;
-    if (active) {
+    if (one) {
+        if (active) {
+            if (y0 & 1) met_quad<Q, PO, R, LE>(a, rs, tb, t, y0, x4, cur, wsum, ragged);
+            else met_quad<Q, PE, R, LE>(a, rs, tb, t, y0, x4, cur, wsum, ragged);
+        }
+    } else if (active) {
         const ProgressPrio<true> prio((y1 - y0) >> 1);
         for (uint32_t y = y0; y < y1; y += 2) {
             prio.step((y - y0) >> 1);
-            const QuadBytes odd = met_load4<PO, R, true>(a, rs, y + 1, x4, x4h, xl, xr);
-            met_quad<Q, PE, R, false, LE>(a, rs, tb, t, y, x4, cur, wsum, ragged);
+            const QuadBytes odd = met_load4<PO, R>(a, rs, y + 1, x4, x4h, xl, xr);
+            met_quad<Q, PE, R, LE>(a, rs, tb, t, y, x4, cur, wsum, ragged);
             const uint32_t yn = (y + 2 < y1) ? y + 2 : y;
-            cur = met_load4<PE, R, false>(a, rs, yn, x4, x4h, xl, xr);
-            met_quad<Q, PO, R, true, LE>(a, rs, tb, t, y + 1, x4, odd, wsum, ragged);
+            cur = met_load4<PE, R>(a, rs, yn, x4, x4h, xl, xr);
+            met_quad<Q, PO, R, LE>(a, rs, tb, t, y + 1, x4, odd, wsum, ragged);
         }
     }
     met_reduce(wsum, a.slots + KAPPA * kBankSlots, blockIdx.x + blockIdx.y * gridDim.x);
@@ -499,15 +486,49 @@ __device__ __forceinline__ uint32_t batch_chain(const uint32_t* start, uint32_t 
 // Batched colour pass: many independent chains of uneven L in one launch.
 // Workgroup b belongs to the chain c with start[c] <= b < start[c+1].
 // A chain's colour pass is cut into work units -- a row pair (2 rp, 2 rp + 1)
-// times a column quad (L % 4 == 0) or a column pair (L % 4 == 2) -- numbered
-// row pair major, and lane l of wavefront w of the chain's workgroup k moves
-// the units (4 k + w) 64 K + l + 64 i, i < K.  No lane idles on a short row:
-// a wavefront spans as many rows as 64 units cover (four row pairs of an
-// L = 64 lattice), and only the chain's last wavefront can run out of units.
+// times a column quad -- numbered row pair major, and lane l of wavefront w of
+// the chain's workgroup k moves the units (4 k + w) 64 K + l + 64 i, i < K.  No
+// lane idles on a short row: a wavefront spans as many rows as 64 units cover
+// (four row pairs of an L = 64 lattice), and only the chain's last wavefront
+// can run out of units.
 // Every unit is moved exactly as the chain's own launch moves it (same
 // Philox counters, same update order inside a cell; cells of one colour do
 // not interact), so each chain follows its standalone trajectory bit for bit.
 // ---------------------------------------------------------------------------
+template <int Q, int KAPPA, bool LE, bool R>
+__device__ __forceinline__ void batch_units(const LatticeArgs& a, uint2* tbl, int theta, uint32_t t, uint32_t first,
+                                            uint32_t K, uint32_t units, uint32_t upr, double upr_inv, uint32_t& wsum)
+{
+    constexpr int PE = KAPPA, PO = 1 - KAPPA;
+    const uint32_t L = a.L;
+    const __amdgpu_buffer_rsrc_t rs = sigma_rsrc(a.sigma, 4 * a.N);
+    // unit u: rows y, y + 1, columns x4 .. x4 + 3 (R: two in the last unit of a row pair)
+    auto load = [&](auto parity, uint32_t y, uint32_t x4) {
+        const uint32_t xl = (x4 == 0) ? L - 1 : x4 - 1, xr = (x4 + 4 >= L) ? 0 : x4 + 4;
+        const uint32_t x4h = R && x4 + 2 == L ? x4 : x4 + 2;
+        return met_load4<decltype(parity)::value, R, true>(a, rs, y, x4, x4h, xl, xr);
+    };
+    uint32_t qd, y = 2 * divmod(first, upr, upr_inv, qd), x4 = 4 * qd;
+    QuadBytes cur = {};
+    if (first < units) cur = load(std::integral_constant<int, PE>(), y, x4);
+    met_table<LE>(a, tbl, theta);
+    for (uint32_t i = 0; i < K; ++i) {
+        const uint32_t u = first + 64 * i;
+        const bool act = u < units, ragged = R && x4 + 2 == L;
+        QuadBytes odd = {};
+        if (act) {
+            odd = load(std::integral_constant<int, PO>(), y + 1, x4);
+            met_quad<Q, PE, R, LE, true>(a, rs, tbl, t, y, x4, cur, wsum, ragged);
+        }
+        const uint32_t un = u + 64;
+        const uint32_t yn = 2 * divmod(un, upr, upr_inv, qd), xn = 4 * qd;
+        if (i + 1 < K && un < units) cur = load(std::integral_constant<int, PE>(), yn, xn);
+        if (act) met_quad<Q, PO, R, LE, true>(a, rs, tbl, t, y + 1, x4, odd, wsum, ragged);
+        y = yn;
+        x4 = xn;
+    }
+}
+
 // Batches are mostly small lattices: the 8-wavefront occupancy measured
 // faster than the uncapped register budget.
 template <int Q, int KAPPA, bool LE>
@@ -542,79 +563,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t first = (local * 4 + wave) * 64 * K + lane;
-    const uint32_t L = a.L;
-    const __amdgpu_buffer_rsrc_t rs = sigma_rsrc(a.sigma, 4 * a.N);
     uint32_t wsum = 0;
-    if (a.quad) {
-        constexpr int PE = KAPPA, PO = 1 - KAPPA;
-        auto at = [&](uint32_t u, uint32_t& y, uint32_t& x4, uint32_t& xl, uint32_t& xr) {
-            uint32_t qd;
-            y = 2 * divmod(u, upr, upr_inv, qd);
-            x4 = 4 * qd;
-            xl = (x4 == 0) ? L - 1 : x4 - 1;
-            xr = (x4 + 4 >= L) ? 0 : x4 + 4;
-        };
-        uint32_t y, x4, xl, xr;
-        at(first, y, x4, xl, xr);
-        QuadBytes cur = {};
-        if (first < units) cur = met_load4<PE, false, false, true>(a, rs, y, x4, x4 + 2, xl, xr);
-        met_table<LE>(a, tbl, theta);
-        for (uint32_t i = 0; i < K; ++i) {
-            const uint32_t u = first + 64 * i;
-            const bool act = u < units;
-            QuadBytes odd = {};
-            if (act) {
-                odd = met_load4<PO, false, true, true>(a, rs, y + 1, x4, x4 + 2, xl, xr);
-                met_quad<Q, PE, false, false, LE, true>(a, rs, tbl, t, y, x4, cur, wsum, false);
-            }
-            const uint32_t un = u + 64;
-            uint32_t yn, x4n, xln, xrn;
-            at(un, yn, x4n, xln, xrn);
-            if (i + 1 < K && un < units) cur = met_load4<PE, false, false, true>(a, rs, yn, x4n, x4n + 2, xln, xrn);
-            if (act) met_quad<Q, PO, false, true, LE, true>(a, rs, tbl, t, y + 1, x4, odd, wsum, false);
-            y = yn;
-            x4 = x4n;
-            xl = xln;
-            xr = xrn;
-        }
-    } else {
-        // column pairs: the updated cell of a pair sits at column 2 pr + KAPPA
-        // in even rows and 2 pr + 1 - KAPPA in odd rows
-        auto at = [&](uint32_t u, uint32_t& y, uint32_t& pr) { y = 2 * divmod(u, upr, upr_inv, pr); };
-        auto nb = [&](uint32_t x, uint32_t& xp, uint32_t& xm) {
-            xp = (x + 1 == L) ? 0 : x + 1;
-            xm = (x == 0) ? L - 1 : x - 1;
-        };
-        uint32_t y, pr, xp, xm;
-        at(first, y, pr);
-        CellBytes cur = {};
-        if (first < units) {
-            nb(2 * pr + KAPPA, xp, xm);
-            cur = met_load<true>(a, rs, y, 2 * pr + KAPPA, xp, xm);
-        }
-        met_table<LE>(a, tbl, theta);
-        for (uint32_t i = 0; i < K; ++i) {
-            const uint32_t u = first + 64 * i;
-            const bool act = u < units;
-            const uint32_t xA = 2 * pr + KAPPA, xB = 2 * pr + (1 - KAPPA);
-            CellBytes odd = {};
-            if (act) {
-                nb(xB, xp, xm);
-                odd = met_load<true>(a, rs, y + 1, xB, xp, xm);
-                met_cell<Q, true, LE>(a, rs, tbl, t, y, xA, cur, wsum);
-            }
-            const uint32_t un = u + 64;
-            uint32_t yn, prn;
-            at(un, yn, prn);
-            if (i + 1 < K && un < units) {
-                nb(2 * prn + KAPPA, xp, xm);
-                cur = met_load<true>(a, rs, yn, 2 * prn + KAPPA, xp, xm);
-            }
-            if (act) met_cell<Q, true, LE>(a, rs, tbl, t, y + 1, xB, odd, wsum);
-            y = yn;
-            pr = prn;
-        }
-    }
+    if (a.quad == 1) batch_units<Q, KAPPA, LE, false>(a, tbl, theta, t, first, K, units, upr, upr_inv, wsum);
+    else batch_units<Q, KAPPA, LE, true>(a, tbl, theta, t, first, K, units, upr, upr_inv, wsum);
     met_reduce(wsum, a.slots + KAPPA * kBankSlots, local);
 }
 

@@ -284,13 +284,8 @@ __global__ __launch_bounds__(kBlock) void pass3_kernel(Lat3 a_, PassShape sh)
     // word whose sums over 64 lanes stay below 2^16.
     static_assert(kMaxQuadsPerLane <= 4, "the halves below hold 48 moves per lane");
     const int acc = (int)(sums.bits / 8), dc = ((int)sums.dc - 64 * acc) / 8, dh = (int)sums.ho - (int)sums.hn;
-    uint32_t v = (uint32_t)(dc + 240) | ((uint32_t)(dh + 48) << 16);
-    int na = acc;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        v += (uint32_t)__shfl_xor((int)v, o, 64);
-        na += __shfl_xor(na, o, 64);
-    }
+    const uint32_t v = (uint32_t)wave_sum((int)((uint32_t)(dc + 240) | ((uint32_t)(dh + 48) << 16)));
+    const int na = wave_sum(acc);
     __shared__ int part[3][kBlock / 64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (lane == 0) {

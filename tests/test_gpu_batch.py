@@ -272,3 +272,29 @@ def test_batch_create_async_and_observables_async(cvf):
         x.close()
     for ch in a + b:
         ch.close()
+
+
+@pytest.mark.parametrize("algo", ["met", "sw"])
+def test_batch_across_the_liquid_limit(cvf, algo):
+    """Batched steps are opened beside the step before them; chains that cross
+    v = 2 again and again follow the trajectory they have alone, one call per
+    step (where every step is opened with N_HB_raw known), also from a graph."""
+    Ls = [4, 6, 34, 64, 66, 130]
+    def mk(L):
+        p = cvf.cvf_params_from_si(300.0, 0.1, L=L, seed=60 + L, v_init=1.98, dv_max=0.3)
+        p.beta, p.J, p.P, p.vHB = 1.0 / (L * L), 2.0, 0.5, 0.3
+        return cvf.Chain(p)
+
+    alone, chains = [mk(L) for L in Ls], [mk(L) for L in Ls]
+    for ch in alone:
+        for _ in range(41):
+            getattr(ch, "metropolis" if algo == "met" else "sw")(1)
+    b = cvf.Batch(chains)
+    if algo == "met":
+        b.metropolis(5, 0).metropolis(36, 9)
+    else:
+        b.sw(5).sw(36)
+    for L, x, y in zip(Ls, alone, chains):
+        assert digest(x) == digest(y), L
+        assert x.obs() == y.obs(), L
+    b.close()

@@ -277,3 +277,35 @@ def test_recount_of_the_lattice(cvf, L):
         assert o["count"] == [int((s == k).sum()) for k in range(6)]
         assert o["consistent"] == 1
     ch.close()
+
+
+@pytest.mark.parametrize("L", [4, 12, 252, 1020, 1026, 1498, 2044, 2046, 2048, 2050])
+def test_metropolis_shapes_at_their_limits(cvf, oracle_mod, L):
+    """One row per wavefront up to L = 2046 and row blocks from there, with
+    dword rows and (from L = 1026, L % 4 == 2) rows off a dword boundary whose
+    last quad has two cells; q = 4 has no word without a proposal, q = 6 has."""
+    for q in (4, 6):
+        op = oracle_mod.params_from_si(300.0, 0.1, L=L, q=q, seed=1300 + L + q)
+        run_pair(cvf, oracle_mod, op, [("met", 2)], algo_mask=1)
+
+
+@pytest.mark.parametrize("algo", ["met", "dom", "sw"])
+@pytest.mark.parametrize("L", [4, 34, 66])
+def test_volume_moves_across_the_liquid_limit(cvf, oracle_mod, algo, L):
+    """Steps opened beside the step before them: moves that propose to cross
+    v = 2 wait for N_HB_raw, in the middle of a call and in its first and last
+    step; the trajectory is the oracle's, which crosses in both directions."""
+    step = {"met": "metropolis", "dom": "metropolis_domain", "sw": "sw"}[algo]
+
+    def crossings(op):
+        oc = oracle_mod.Chain(op)
+        theta = []
+        for _ in range(60):
+            getattr(oc, step)(1)
+            theta.append(oc.obs()["v"] < 2.0)
+        return sum(a != b for a, b in zip(theta, theta[1:]))
+
+    ops = (oracle_mod.make_params(L=L, q=6, beta=1.0 / (L * L), J=2.0, Jsigma=0.3, P=0.5, vHB=0.3, v_init=1.98,
+                                  dv_max=0.3, seed=1400 + k) for k in range(40))
+    op = next(op for op in ops if crossings(op) >= 4)
+    run_pair(cvf, oracle_mod, op, [(algo, 1), (algo, 2), (algo, 57)])
