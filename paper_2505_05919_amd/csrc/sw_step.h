@@ -168,15 +168,34 @@ __device__ __forceinline__ uint32_t tile_global(const TileGeom& g, uint32_t L, u
     return (v / kTC) * N + (g.y0 + lc / kTW) * L + g.x0 + lc % kTW;
 }
 
-// The 4 kTC / kTT = 16 bond indices of a thread: entry i lies in plane i / 4,
-// tile row wave + W (i % 4) (wave-uniform; W = kTT / 64 wavefronts, so the
-// four rows of a wavefront cover the kTH = 4 W rows of the tile) and tile
-// column lane.
-__device__ __forceinline__ uint32_t ent_row(uint32_t wave, uint32_t i) { return wave + (kTT / 64) * (i & 3); }
-__device__ __forceinline__ uint32_t ent_local(uint32_t wave, uint32_t lane, uint32_t i)
+// The 16 bond indices of a thread: four neighbouring cells of one tile row,
+// in each of the four planes.  A tile row is 16 lanes, so the cells to the
+// right are the next lane's, and a plane's four sigma are one dword and its
+// four local roots two; rows start at even addresses, which wider accesses take.
+// Against one bond index per lane and access (16 byte and 16 half-word loads
+// or stores, and the new sigma through LDS twice) the flip went from 20.4 to
+// 17.3 us at L = 1414, from 8.8 to 6.5 us at L = 256 and from 35.4 to 29.2 us
+// for 100 mixed lattices; the tile kernel stayed at 25.5 us, the time of its
+// two Philox calls per cell.
+struct QuadPos {
+    uint32_t lx, ly, lc;  // first cell: tile column, tile row, local index (4 threadIdx.x)
+    uint32_t c;           // its global index (0 if none is inside)
+    uint32_t n;           // cells inside the tile: 0, 2 or 4, for L is even
+};
+static_assert(kTT * 4 == kTC && kTW == 64, "16 threads per tile row");
+
+__device__ __forceinline__ QuadPos quad_pos(const TileGeom& g, uint32_t L)
 {
-    return (i >> 2) * kTC + ent_row(wave, i) * kTW + lane;
+    QuadPos q;
+    q.lc = 4 * threadIdx.x;
+    q.lx = q.lc % kTW;
+    q.ly = q.lc / kTW;
+    q.n = q.ly < g.h && q.lx < g.w ? min(4u, g.w - q.lx) : 0u;
+    q.c = q.n ? (g.y0 + q.ly) * L + g.x0 + q.lx : 0u;
+    return q;
 }
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // The border bond indices of a tile -- the ends of tile-crossing covalent
 // links -- numbered b < 2 kTH + 2 kTW: arm 0 in the last column and arm 1 in
@@ -359,12 +378,12 @@ __device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const VolArgs
     // (a root's entry is the root | flag, so nearly every index is settled by
     // these two reads); the few longer chains are followed in lockstep.
     // Rows past a ragged tile's end hold singletons and are read, not stored.
-    const uint32_t voff = 2 * vx;
+    const QuadPos qp = quad_pos(g, L);
 #pragma unroll
     for (uint32_t h = 0; h < 2; ++h) {
         uint32_t r[8], e[8];
 #pragma unroll
-        for (uint32_t j = 0; j < 8; ++j) r[j] = lab[(2 * h + (j >> 2)) * kTC + (j & 3) * kTT + threadIdx.x] & kIdx;
+        for (uint32_t j = 0; j < 8; ++j) r[j] = lab[(2 * h + (j >> 2)) * kTC + qp.lc + (j & 3)] & kIdx;
 #pragma unroll
         for (uint32_t j = 0; j < 8; ++j) e[j] = lab[r[j]];
         for (;;) {
@@ -379,20 +398,24 @@ __device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const VolArgs
             }
         }
 #pragma unroll
-        for (uint32_t j = 0; j < 8; ++j) {
-            const uint32_t p = 2 * h + (j >> 2), ly = ent_row(wave, j & 3);
-            if (ly < g.h && col_in) {
-                const __amdgpu_buffer_rsrc_t rl = buf_rsrc(a.lroot + (size_t)p * N, 2 * N);
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)e[j], rl, (int)voff, (int)(2 * (g.y0 + ly) * L),
-                                                      kThrough);
-                const uint32_t v = p * kTC + ly * kTW + lane;
-                if (r[j] == v && (e[j] & kBorder)) {
+        for (uint32_t b = 0; b < 2; ++b) {
+            const uint32_t p = 2 * h + b;
+            const uint32_t* eb = e + 4 * b;
+            const __amdgpu_buffer_rsrc_t rl = buf_rsrc(a.lroot + (size_t)p * N, 2 * N);
+            if (qp.n == 4) {
+                const u32x2 w = {eb[0] | eb[1] << 16, eb[2] | eb[3] << 16};
+                __builtin_amdgcn_raw_buffer_store_b64(w, rl, (int)(2 * qp.c), 0, kThrough);
+            } else if (qp.n) {
+                __builtin_amdgcn_raw_buffer_store_b32(eb[0] | eb[1] << 16, rl, (int)(2 * qp.c), 0, kThrough);
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j)
+                if (j < qp.n && eb[j] == (kBorder | (p * kTC + qp.lc + j))) {
                     // a root other tiles' unions may reach this step: written
                     // through to the device-coherent level (see below)
-                    const uint32_t gv = tile_global(g, L, N, v);
+                    const uint32_t gv = p * N + qp.c + j;
                     __hip_atomic_store(a.label + gv, gv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-            }
         }
     }
     // Tile-crossing links.  Every border bond index gets the global label of
@@ -476,20 +499,19 @@ __global__ __launch_bounds__(kTT) void sw_tile_kernel(LatticeArgs a, VolArgs va,
     sw_tile_body(a, va, ctl.bank, grid_tile(a.L, gridDim.y), lut, lab, act);
 }
 
-// LDS of the flip: the compacted roots of the interior components, whose
-// space then holds the new sigma of the tile; the shift of each root; the
-// old (then new) sigma of the tile, kept here rather than in registers so
-// that the kernel fits 8 wavefronts per SIMD; the compacted roots of the
-// border components (at most one per border bond index); the new sigma
-// facing the right / bottom edge; the two root counts.
+// LDS of the flip: the compacted roots of the interior components; the shift
+// of each root; the new sigma of arm 3; the new sigma facing the right /
+// bottom edge; the compacted roots of the border components (at most one per
+// border bond index); the two root counts.
 struct FlipLds {
     uint16_t roots[4 * kTC];
     uint8_t sh[4 * kTC];
-    uint8_t osg[4 * kTC];
+    uint32_t up[kTC / 4];
+    __align__(4) uint8_t across[kEdgeBytes];
     uint16_t rootb[kBorderIdx];
-    uint8_t across[kEdgeBytes];
     uint32_t nroot, nrootb;
 };
+static_assert(kTH % 4 == 0, "four columns of the bottom edge's facing arms are one aligned word");
 
 // Exclusive prefix sum over the wavefront of per-lane values c < 32, and
 // its total: one ballot per bit.
@@ -512,29 +534,29 @@ __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, uint32_t bank
     uint8_t* sh = lds.sh;
     uint8_t* across = lds.across;
     uint16_t* rootb = lds.rootb;
-    uint8_t* nsg = reinterpret_cast<uint8_t*>(roots);
     if (threadIdx.x == 0) {
         lds.nroot = 0;
         lds.nrootb = 0;
     }
     const uint32_t L = a.L, N = a.N, q = a.q;
-    // entry i: plane i / 4, tile row ent_row(wave, i), column lane
-    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool col_in = lane < g.w;
-    const uint32_t voff = col_in ? g.x0 + lane : 0u;
+    // entry i: plane i / 4, cell i % 4 of the thread's four
+    const uint32_t lane = threadIdx.x & 63;
+    const QuadPos qp = quad_pos(g, L);
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(a.sigma, 4 * N);
-    uint32_t os[4 * kTC / kTT], lr[4 * kTC / kTT];     // old sigma, local root | kBorder
+    uint32_t os[4], lrp[8];                   // old sigma; local roots | kBorder, two per register
 #pragma unroll
-    for (uint32_t i = 0; i < 4 * kTC / kTT; ++i) {
-        const uint32_t p = i >> 2, ly = ent_row(wave, i);
-        os[i] = 0;
-        lr[i] = ent_local(wave, lane, i);
-        if (ly < g.h) {
-            const uint32_t row = (g.y0 + ly) * L;
-            os[i] = __builtin_amdgcn_raw_buffer_load_b8(rs, (int)voff, (int)(p * N + row), 0);
-            const uint32_t l = __builtin_amdgcn_raw_buffer_load_b16(buf_rsrc(a.lroot + (size_t)p * N, 2 * N),
-                                                                   (int)(2 * voff), (int)(2 * row), 0);
-            if (col_in) lr[i] = l;
+    for (uint32_t p = 0; p < 4; ++p) {
+        os[p] = 0;
+        lrp[2 * p] = lrp[2 * p + 1] = 0;
+        const __amdgpu_buffer_rsrc_t rl = buf_rsrc(a.lroot + (size_t)p * N, 2 * N);
+        if (qp.n == 4) {
+            os[p] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)qp.c, (int)(p * N), 0);
+            const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rl, (int)(2 * qp.c), 0, 0);
+            lrp[2 * p] = w.x;
+            lrp[2 * p + 1] = w.y;
+        } else if (qp.n) {
+            os[p] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)qp.c, (int)(p * N), 0);
+            lrp[2 * p] = __builtin_amdgcn_raw_buffer_load_b32(rl, (int)(2 * qp.c), 0, 0);
         }
     }
     // the loads above do not depend on the chain state; read it now
@@ -548,12 +570,6 @@ __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, uint32_t bank
         static_assert(kTT >= 2 * kSlots, "one thread per slot of the two recounted values");
         if (threadIdx.x < 2 * kSlots) a.slots[(bank ^ 1u) * kBankSlots + threadIdx.x] = 0;
     }
-#pragma unroll
-    for (uint32_t i = 0; i < 4 * kTC / kTT; ++i) lds.osg[ent_local(wave, lane, i)] = (uint8_t)os[i];
-    // the 16-bit local roots, two per register for the rest of the kernel
-    uint32_t lrp[2 * kTC / kTT];
-#pragma unroll
-    for (uint32_t k = 0; k < 2 * kTC / kTT; ++k) lrp[k] = lr[2 * k] | (lr[2 * k + 1] << 16);
     auto LR = [&](uint32_t i) { return (lrp[i >> 1] >> (16 * (i & 1))) & 0xFFFFu; };
     // component roots, compacted into an interior and a border list: a lane's
     // slots follow from a prefix sum of the per-lane counts over the
@@ -567,7 +583,7 @@ __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, uint32_t bank
     uint32_t rf = 0;
 #pragma unroll
     for (uint32_t i = 0; i < 4 * kTC / kTT; ++i) {
-        const bool root = col_in && ent_row(wave, i) < g.h && (LR(i) & kIdx) == ent_local(wave, lane, i);
+        const bool root = (i & 3) < qp.n && (LR(i) & kIdx) == (i >> 2) * kTC + qp.lc + (i & 3);
         const uint32_t bit = ((LR(i) >> 11) & 16u) + i;   // the border flag (bit 15) selects bit 16 + i
         rf |= (root ? 1u : 0u) << bit;
     }
@@ -644,35 +660,45 @@ __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, uint32_t bank
     // the packed registers instead of being kept live (and spilled) across
     // the draws since the compaction.
 #pragma unroll
-    for (uint32_t k = 0; k < 2 * kTC / kTT; ++k) __asm__("" : "+v"(lrp[k]));
+    for (uint32_t k = 0; k < 8; ++k) __asm__("" : "+v"(lrp[k]));
+    // New sigma, four cells to a word: byte sums stay below 16, and bit 7 of
+    // (sum + 128 - q) says whether to take q off.
+    const uint32_t one = 0x01010101u, qv = q * one, lift = (128u - q) * one;
+    const uint32_t in = qp.n == 4 ? ~0u : (1u << (8 * qp.n)) - 1u;   // bytes of cells inside the tile
+    uint32_t ns[4];
 #pragma unroll
-    for (uint32_t i = 0; i < 4 * kTC / kTT; ++i) {
-        const uint32_t ly = ent_row(wave, i);
-        uint32_t s = lds.osg[ent_local(wave, lane, i)] + sh[LR(i) & kIdx];
-        s = s >= q ? s - q : s;
-        if (col_in && ly < g.h)
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)s, rs, (int)voff, (int)((i >> 2) * N + (g.y0 + ly) * L),
-                                                 kThrough);
-        lds.osg[ent_local(wave, lane, i)] = (uint8_t)s;
-    }
-    __syncthreads();                          // the root list is dead: its space holds the new sigma
+    for (uint32_t p = 0; p < 4; ++p) {
+        uint32_t d = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < 4 * kTC / kTT; ++i) nsg[ent_local(wave, lane, i)] = lds.osg[ent_local(wave, lane, i)];
-    __syncthreads();
-    // recount of the new configuration: the +x and +y HB pairs and the six
-    // in-cell pairs of every cell of the tile
-    int hb = 0, co = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < kTC / kTT; ++i) {
-        const uint32_t lc = threadIdx.x + kTT * i, lx = lc % kTW, ly = lc / kTW;
-        if (lx < g.w && ly < g.h) {
-            const uint32_t s0 = nsg[lc], s1 = nsg[kTC + lc], s2 = nsg[2 * kTC + lc], s3 = nsg[3 * kTC + lc];
-            const uint32_t f0 = lx + 1 < g.w ? nsg[kTC + lc + 1] : across[ly];
-            const uint32_t f2 = ly + 1 < g.h ? nsg[3 * kTC + lc + kTW] : across[kTH + lx];
-            hb += (s0 == f0) + (s2 == f2);
-            co += (s0 == s1) + (s0 == s2) + (s0 == s3) + (s1 == s2) + (s1 == s3) + (s2 == s3);
+        for (uint32_t j = 0; j < 4; ++j) d |= (uint32_t)sh[LR(4 * p + j) & kIdx] << (8 * j);
+        uint32_t w = os[p] + (d & in);
+        const uint32_t ge = ((w + lift) >> 7) & one;
+        w -= ((ge << 3) - ge) & qv;           // 7 in every byte to lower by q (q <= 6)
+        ns[p] = w;
+        if (qp.n == 4) {
+            __builtin_amdgcn_raw_buffer_store_b32(w, rs, (int)qp.c, (int)(p * N), kThrough);
+        } else if (qp.n) {
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)w, rs, (int)qp.c, (int)(p * N), kThrough);
         }
     }
+    lds.up[threadIdx.x] = ns[3];
+    __syncthreads();
+    // Recount of the new configuration: the +x and +y HB pairs and the six
+    // in-cell pairs of every cell of the tile.  Bit 3 of (x ^ y) + 7 says
+    // that two sigma differ.
+    uint32_t f0 = __builtin_amdgcn_alignbyte((uint32_t)__builtin_amdgcn_update_dpp(0, (int)ns[1], 0x101, 0xf, 0xf, true),
+                                             ns[1], 1);   // arm 1 one cell on (row_shl:1: the next lane's)
+    if (qp.n && qp.lx + qp.n == g.w) {        // the last column faces the next tile
+        const uint32_t sft = 8 * (qp.n - 1);
+        f0 = (f0 & ~(0xFFu << sft)) | ((uint32_t)across[qp.ly] << sft);
+    }
+    const uint32_t f2 = qp.ly + 1 < g.h ? lds.up[threadIdx.x + kTW / 4]
+                                        : *reinterpret_cast<const uint32_t*>(across + kTH + qp.lx);
+    auto differ = [](uint32_t u, uint32_t w) { return ((u ^ w) + 0x07070707u) & 0x08080808u; };
+    const uint32_t dh = differ(ns[0], f0) | differ(ns[2], f2) >> 1;
+    const uint32_t dc = differ(ns[0], ns[1]) | differ(ns[0], ns[2]) >> 1 | differ(ns[0], ns[3]) >> 2 |
+                        differ(ns[1], ns[2]) >> 3 | differ(ns[1], ns[3]) << 1 | differ(ns[2], ns[3]) << 2;
+    const int hb = 2 * (int)qp.n - __popc(dh & in), co = 6 * (int)qp.n - __popc(dc & in);
     const int v2[2] = {hb, co};
     block_add<2, kTT>(v2, a.slots + bank * kBankSlots + (g.id & (kSlots - 1)), kSlots);
 }

@@ -309,3 +309,12 @@ def test_volume_moves_across_the_liquid_limit(cvf, oracle_mod, algo, L):
                                   dv_max=0.3, seed=1400 + k) for k in range(40))
     op = next(op for op in ops if crossings(op) >= 4)
     run_pair(cvf, oracle_mod, op, [(algo, 1), (algo, 2), (algo, 57)])
+
+
+@pytest.mark.parametrize("q", [2, 6])
+@pytest.mark.parametrize("L", [2, 10, 60, 62, 64, 68, 142, 190])
+def test_sw_tiles_at_their_edges(cvf, oracle_mod, L, q):
+    """Tiles whose rows end inside a lane's four cells, at a lane's end and at
+    the tile's own; rows off a dword boundary; first, last and single tiles."""
+    op = oracle_mod.params_from_si(260.0, 0.1, L=L, q=q, seed=1500 + L + q)
+    run_pair(cvf, oracle_mod, op, [("sw", 1), ("sw", 3), ("met", 1), ("sw", 2)], labels=True)
