@@ -734,7 +734,9 @@ def main():
         kt = instrumented(cvf, dch, lambda: run_blocks(dch, "metropolis_domain", K), [cvf.CVF_K_MET_DOMAIN])
         n_pass, pass_ms = kt[cvf.CVF_K_MET_DOMAIN]
         # one pass moves one arm of every cell: N updates, 6 algorithmic bytes
-        # each (the cell's four bond indices and the facing one read, one written)
+        # each (the cell's four bond indices and the facing one read, one
+        # written); a sweep's four passes take three launches
+        n_pass, pass_ms = n_pass * 4 // 3, pass_ms * 3 / 4
         pass_s = pass_ms * 1e-3
         dom_tops = N * ALU_OPS_PER_UPDATE / pass_s / 1e12
         dom_gbs = N * 6 / pass_s / 1e9

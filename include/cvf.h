@@ -244,7 +244,7 @@ int cvf_tables(const cvf_state *st, uint32_t met[2][3][7], uint64_t sw[3]);
                                launch (value kept for the ABI)     */
 #define CVF_K_SW_FLIP   4   /* cluster shift + recount             */
 #define CVF_K_RECOUNT   5   /* lattice recount (separate launches) */
-#define CVF_K_MET_DOMAIN 6  /* one arm-domain pass                 */
+#define CVF_K_MET_DOMAIN 6  /* one arm-domain launch (three a sweep) */
 #define CVF_K_COUNT     7
 int cvf_timing_enable(cvf_state *st, int enable);
 int cvf_kernel_times(cvf_state *st, int kind, int64_t *launches, double *mean_ms);

@@ -331,9 +331,9 @@ int cvf_metropolis_domain_sweeps(cvf_state* st, int64_t nsweeps, void* stream)
     v.met_att_add = 4 * (int64_t)st->N;
     if (nsweeps > 0) TIMED(CVF_K_VOLUME, launch_volume, v, s);
     for (int64_t i = 0; i < nsweeps; ++i)
-        for (uint32_t pass = 0; pass < 4; ++pass) {
-            const StepCtl c = {(uint32_t)(i & 1), pass == 3 && i + 1 < nsweeps ? 1u : 0u};
-            TIMED(CVF_K_MET_DOMAIN, launch_met_domain, st->la, v, c, pass, s);
+        for (uint32_t group = 0; group < 3; ++group) {
+            const StepCtl c = {(uint32_t)(i & 1), group == 2 && i + 1 < nsweeps ? 1u : 0u};
+            TIMED(CVF_K_MET_DOMAIN, launch_met_domain, st->la, v, c, group, s);
         }
     return CVF_OK;
 }

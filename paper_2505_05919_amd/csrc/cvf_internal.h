@@ -204,8 +204,9 @@ hipError_t launch_sigma_init(const LatticeArgs& a, hipStream_t s);
 hipError_t launch_volume(const VolArgs& a, hipStream_t s, DispatchEvents ev = {});
 hipError_t launch_met_colour(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, hipStream_t s,
                              DispatchEvents ev = {});
-// Arm-domain sweep: pass 0..3 of the step's drawn arm order (any L >= 2).
-hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t pass, hipStream_t s,
+// Arm-domain sweep: launch group 0..2 of a step, each of at most two arms (any
+// L >= 2).
+hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t group, hipStream_t s,
                              DispatchEvents ev = {});
 // N_HB_raw and N_sigma of the lattice added to the counter slots.
 hipError_t launch_recount(const LatticeArgs& a, int64_t* slots, hipStream_t s);

@@ -503,31 +503,31 @@ hipError_t launch_set_stop(DevState* st, int64_t stop_at, hipStream_t s)
 }
 
 template <int Q>
-hipError_t launch_domain_q(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t pass, dim3 grid, uint32_t rows,
+hipError_t launch_domain_q(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t group, dim3 grid, uint32_t rows,
                            hipStream_t s, const DispatchEvents& ev)
 {
-    if (a.L % 4 == 0) return go(met_domain_kernel<Q, 2>, grid, dim3(256), s, ev, a, v, c, pass, rows);
-    if (a.L % 2 == 0) return go(met_domain_kernel<Q, 1>, grid, dim3(256), s, ev, a, v, c, pass, rows);
-    return go(met_domain_kernel<Q, 0>, grid, dim3(256), s, ev, a, v, c, pass, rows);
+    if (a.L % 4 == 0) return go(met_domain_kernel<Q, 0>, grid, dim3(256), s, ev, a, v, c, group, rows);
+    if (a.L > 4) return go(met_domain_kernel<Q, 1>, grid, dim3(256), s, ev, a, v, c, group, rows);
+    return go(met_domain_kernel<Q, 2>, grid, dim3(256), s, ev, a, v, c, group, rows);
 }
 
-hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t pass, hipStream_t s,
+hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t group, hipStream_t s,
                              DispatchEvents ev)
 {
-    // lanes own column quads (L % 4 == 0) or pairs, (L + 1) / 2 per row; rows
-    // per wavefront for ~8192 wavefronts (measured at L = 4096 with pairs:
-    // 515 vs 458 updates/ns for 4096)
-    const uint32_t lanes = (a.L % 4 == 0) ? a.L / 4 : (a.L + 1) / 2;
-    const uint32_t groups = (lanes + 63) / 64;
-    const uint32_t wpg = groups >= 8192 ? 1 : 8192 / groups;
-    const uint32_t rows = min(32u, (a.L + wpg - 1) / wpg);
-    const dim3 grid(groups, ((a.L + rows - 1) / rows + 3) / 4 + c.open);
+    // lanes own column quads; rows per lane for ~8192 wavefronts (measured at
+    // L = 4096 with pairs: 515 vs 458 updates/ns for 4096), at most 16: the
+    // 10-bit counter field of a lane takes 170 moves, a row has up to 8
+    const uint64_t quads = (a.L + 3) / 4;
+    const uint64_t waves = (quads * a.L + 63) / 64;
+    const uint32_t rows = (uint32_t)std::min<uint64_t>(16, (waves + 8191) / 8192);
+    const uint64_t units = quads * ((a.L + rows - 1) / rows);
+    const dim3 grid((uint32_t)((units + 255) / 256) + c.open);
     switch (a.q) {
-    case 2: return launch_domain_q<2>(a, v, c, pass, grid, rows, s, ev);
-    case 3: return launch_domain_q<3>(a, v, c, pass, grid, rows, s, ev);
-    case 4: return launch_domain_q<4>(a, v, c, pass, grid, rows, s, ev);
-    case 5: return launch_domain_q<5>(a, v, c, pass, grid, rows, s, ev);
-    default: return launch_domain_q<6>(a, v, c, pass, grid, rows, s, ev);
+    case 2: return launch_domain_q<2>(a, v, c, group, grid, rows, s, ev);
+    case 3: return launch_domain_q<3>(a, v, c, group, grid, rows, s, ev);
+    case 4: return launch_domain_q<4>(a, v, c, group, grid, rows, s, ev);
+    case 5: return launch_domain_q<5>(a, v, c, group, grid, rows, s, ev);
+    default: return launch_domain_q<6>(a, v, c, group, grid, rows, s, ev);
     }
 }
 

@@ -126,3 +126,14 @@ def test_domain_step_limit_and_zero_sweeps(cvf, oracle_mod):
     for k in ("n_hb_raw", "n_coop", "count", "met_accepted", "vol_accepted"):
         assert og[k] == oo[k], k
     ch.close()
+
+
+@pytest.mark.parametrize("L", [6, 9, 255, 256, 259, 514, 2046, 2049, 2051])
+def test_domain_launch_groups(cvf, oracle_mod, L):
+    """Steps whose drawn order shares launches as 2 + 2 arms and as 1 + 2 + 1;
+    rows that end inside a lane's four columns, wavefronts that cross row
+    ends, and from L = 2046 several rows per lane with a ragged last band."""
+    q = 2 + L % 5
+    op = oracle_mod.params_from_si(285.0, 25.0, L=L, q=q, seed=1600 + L)
+    run_pair(cvf, oracle_mod, op, [("dom", 1), ("dom", 1), ("dom", 2 if L > 1000 else 14)],
+             algo_mask=cvf.CVF_ALGO_METROPOLIS)
