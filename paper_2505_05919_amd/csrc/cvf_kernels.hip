@@ -514,12 +514,15 @@ hipError_t launch_domain_q(const LatticeArgs& a, const VolArgs& v, StepCtl c, ui
 hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, uint32_t group, hipStream_t s,
                              DispatchEvents ev)
 {
-    // lanes own column quads; rows per lane for ~8192 wavefronts (measured at
-    // L = 4096 with pairs: 515 vs 458 updates/ns for 4096), at most 16: the
-    // 10-bit counter field of a lane takes 170 moves, a row has up to 8
+    // lanes own column quads; rows per lane for at most 5000 wavefronts, up to
+    // 8 (a lane's 10-bit counter fields take 170 moves, a row has up to 8).
+    // Measured, us per sweep: one / two rows 20.5 / 21.0 at L = 1025 (4126
+    // wavefronts of one row) and 28.9 / 25.2 at L = 1414 (7821); two / four
+    // 34.9 / 33.9 at L = 2048; four / eight / sixteen 97.1 / 94.3 / 99.2 at
+    // L = 4096
     const uint64_t quads = (a.L + 3) / 4;
     const uint64_t waves = (quads * a.L + 63) / 64;
-    const uint32_t rows = (uint32_t)std::min<uint64_t>(16, (waves + 8191) / 8192);
+    const uint32_t rows = (uint32_t)std::min<uint64_t>(8, (waves + 4999) / 5000);
     const uint64_t units = quads * ((a.L + rows - 1) / rows);
     const dim3 grid((uint32_t)((units + 255) / 256) + c.open);
     switch (a.q) {
