@@ -240,8 +240,8 @@ void chain_setup(const cvf_params* p, uint8_t* d_sigma, char* work, size_t work_
     a.flip_invd = 1.0 / (double)dq;
     {
         const MetShape m = met_shape(a.L);
-        a.quad = m.quad;
-        const bool one = met_one_row(a.L, m);
+        a.quad = a.L % 4 == 0 ? 1 : 2;
+        const bool one = met_one_row(a.L);
         a.rows = one ? 1 : m.rows;
         a.row_blocks = one ? (a.L + 3) / 4 : m.row_blocks;
     }

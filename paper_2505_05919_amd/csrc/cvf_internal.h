@@ -146,7 +146,7 @@ struct LatticeArgs {
     double flip_invd;        // 1 / floor(2^32/q)
     uint32_t rows;           // Metropolis: rows per wavefront (1, or even, <= 32)
     uint32_t row_blocks;     // Metropolis: grid.y
-    uint32_t quad;           // Metropolis: 1 / 2 = dword (4-column) lanes, L % 4 == 0 / 2; 0 = column pairs
+    uint32_t quad;           // Metropolis, 4-column lanes: 1 = L % 4 == 0, 2 = L % 4 == 2
     uint32_t met_le;         // 1: no Metropolis threshold is 0, so acceptance is one compare (word <= thr - 1)
 };
 

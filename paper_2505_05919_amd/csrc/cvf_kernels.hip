@@ -437,23 +437,13 @@ hipError_t launch_quad(const LatticeArgs& a, const VolArgs& v, StepCtl c, int co
 hipError_t launch_met_colour(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, hipStream_t s,
                              DispatchEvents ev)
 {
-    if (a.quad) {
-        const dim3 grid(((a.L + 3) / 4 + 63) / 64, a.row_blocks + c.open);
-        switch (a.q) {
-        case 2: return launch_quad<2>(a, v, c, colour, grid, s, ev);
-        case 3: return launch_quad<3>(a, v, c, colour, grid, s, ev);
-        case 4: return launch_quad<4>(a, v, c, colour, grid, s, ev);
-        case 5: return launch_quad<5>(a, v, c, colour, grid, s, ev);
-        default: return launch_quad<6>(a, v, c, colour, grid, s, ev);
-        }
-    }
-    const dim3 grid((a.L / 2 + 63) / 64, a.row_blocks + c.open), block(256);
+    const dim3 grid(((a.L + 3) / 4 + 63) / 64, a.row_blocks + c.open);
     switch (a.q) {
-    case 2: return go(met_sweep_kernel<2>, grid, block, s, ev, a, v, c, colour);
-    case 3: return go(met_sweep_kernel<3>, grid, block, s, ev, a, v, c, colour);
-    case 4: return go(met_sweep_kernel<4>, grid, block, s, ev, a, v, c, colour);
-    case 5: return go(met_sweep_kernel<5>, grid, block, s, ev, a, v, c, colour);
-    default: return go(met_sweep_kernel<6>, grid, block, s, ev, a, v, c, colour);
+    case 2: return launch_quad<2>(a, v, c, colour, grid, s, ev);
+    case 3: return launch_quad<3>(a, v, c, colour, grid, s, ev);
+    case 4: return launch_quad<4>(a, v, c, colour, grid, s, ev);
+    case 5: return launch_quad<5>(a, v, c, colour, grid, s, ev);
+    default: return launch_quad<6>(a, v, c, colour, grid, s, ev);
     }
 }
 

@@ -18,7 +18,7 @@ namespace cvf {
 // runs beside the launch's arithmetic instead.  Measured: Metropolis sweeps at
 // L = 2048 / 4096 28.3 / 76.8 -> 25.0 / 74.2 us, a Swendsen-Wang step at
 // L = 1414 45.3 -> 42.8 us, cubic passes at 260^3 152.8 -> 151.0 us (sc1 alone
-// the same, nt no change).  Single bytes per lane (column pairs, odd rows,
+// the same, nt no change).  Single bytes per lane (the ends of ragged rows,
 // bond masks) and the cubic shifts stay plain stores: written through, batches of
 // column-pair lattices went from 58 to 60 us and the cubic step from 126.0 to
 // 127.4.

@@ -9,14 +9,7 @@ namespace cvf {
 #ifndef CVF_MET_WAVES
 #define CVF_MET_WAVES 4096
 #endif
-// Use the dword (4-column) Metropolis kernel (1); 0 selects column pairs.
-#ifndef CVF_MET_QUAD
-#define CVF_MET_QUAD 1
-#endif
-// Smallest L % 4 == 2 lattice that a single-chain launch moves in quads (mode
-// 2).  Measured: L = 4094 ~700 vs ~550 updates/ns with column pairs, L = 1414
-// +5 %; at L = 258 the launch is latency-bound and the pairs' twice as many
-// wavefronts win (19 vs 14).
+// Smallest L % 4 == 2 lattice whose shape is made for quads.
 #ifndef CVF_MET_RAGGED_MIN
 #define CVF_MET_RAGGED_MIN 1024
 #endif
@@ -48,21 +41,23 @@ inline MetShape met_shape_mode(uint32_t L, uint32_t quad)
     return m;
 }
 
-// The launch shape of a single chain.
+// The launch shape of a single chain in row blocks.  (Smaller L % 4 == 2
+// lattices have one in column pairs, which is not launched: see below.)
 inline MetShape met_shape(uint32_t L)
 {
-    const uint32_t quad = !CVF_MET_QUAD ? 0 : (L % 4 == 0) ? 1 : (L >= CVF_MET_RAGGED_MIN ? 2 : 0);
+    const uint32_t quad = (L % 4 == 0) ? 1 : (L >= CVF_MET_RAGGED_MIN ? 2 : 0);
     return met_shape_mode(L, quad);
 }
 
-// Largest side whose quads are moved one row per wavefront instead of by the
-// shape above: up to there the launch is bound by a wavefront's latency, not
-// by issue (us per sweep, one row / shape above: L = 256 8.9 / 10.3, L = 1024
-// 11.5 / 13.2, L = 1536 16.7 / 20.5, L = 2048 24.5 / 24.3,
-// L = 4096 79.1 / 72.9).
+// Largest side whose lattice is moved one row of quads per wavefront instead of
+// by the shape above: up to there the launch is bound by a wavefront's latency,
+// not by issue (us per sweep, one row / shape above: L = 256 8.9 / 10.3,
+// L = 1024 11.5 / 13.2, L = 1536 16.7 / 20.5, L = 2048 24.5 / 24.3,
+// L = 4096 79.1 / 72.9; against column pairs L = 66 9.1 / 10.4, L = 258
+// 10.1 / 11.1, L = 1022 12.4 / 18.9).
 #ifndef CVF_MET_ONE_ROW_MAX
 #define CVF_MET_ONE_ROW_MAX 2046
 #endif
-inline bool met_one_row(uint32_t L, const MetShape& m) { return m.quad != 0 && L <= CVF_MET_ONE_ROW_MAX; }
+inline bool met_one_row(uint32_t L) { return L <= CVF_MET_ONE_ROW_MAX; }
 
 }  // namespace cvf

@@ -9,8 +9,7 @@
 // in direction a (J_eff), which has the other colour.
 //
 // Work layout: a lane of a wavefront owns a column quad (4j..4j+3: two cells
-// of the updated colour per row) or, for smaller L % 4 == 2 lattices and
-// batches, a column pair (2i, 2i+1: one cell per row), and walks `rows`
+// of the updated colour per row) and moves one row, or walks `rows`
 // consecutive rows.  Row addresses are wave-uniform (SGPR base + lane
 // column), so the loop carries no vector address arithmetic.
 //
@@ -66,12 +65,6 @@ __device__ __forceinline__ void st8(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32
     __builtin_amdgcn_raw_buffer_store_b8((uint8_t)v, r, (int)voff, (int)soff, 0);
 }
 
-// The eight bytes one cell's update reads: its four arms and the four
-// facing arms of its neighbours (all of the other colour).
-struct CellBytes {
-    uint32_t s0, s1, s2, s3, f0, f1, f2, f3;
-};
-
 // Row offsets go into the wave-uniform scalar offset when y is the same for the
 // whole wavefront, or (VROW) into the per-lane offset when every lane has a row
 // of its own.
@@ -82,49 +75,8 @@ struct RowSplit {
     __device__ __forceinline__ static uint32_t s(uint32_t base, uint32_t o) { return VROW ? base : base + o; }
 };
 
-__device__ __forceinline__ CellBytes met_load(const LatticeArgs& a, __amdgpu_buffer_rsrc_t rs, uint32_t y,
-                                              uint32_t x, uint32_t xp, uint32_t xm)
-{
-    const uint32_t L = a.L, N = a.N;
-    const uint32_t yp = (y + 1 == L) ? 0 : y + 1, ym = (y == 0) ? L - 1 : y - 1;
-    const uint32_t o0 = y * L, op = yp * L, om = ym * L;
-    CellBytes b;
-    b.s0 = ld8(rs, x, o0);
-    b.s1 = ld8(rs, x, N + o0);
-    b.s2 = ld8(rs, x, 2 * N + o0);
-    b.s3 = ld8(rs, x, 3 * N + o0);
-    b.f0 = ld8(rs, xp, N + o0);              // arm 1 of the +x neighbour
-    b.f1 = ld8(rs, xm, o0);                  // arm 0 of the -x neighbour
-    b.f2 = ld8(rs, x, 3 * N + op);           // arm 3 of the +y neighbour
-    b.f3 = ld8(rs, x, 2 * N + om);           // arm 2 of the -y neighbour
-    return b;
-}
-
-// Update the four arms of the cell (x, y) from its loaded bytes and store them.
-template <int Q>
-__device__ __forceinline__ void met_cell(const LatticeArgs& a, __amdgpu_buffer_rsrc_t rs, const uint2* tbl,
-                                         uint32_t t, uint32_t y, uint32_t x, const CellBytes& b, uint32_t& wsum)
-{
-    const uint32_t N = a.N, o0 = y * a.L;
-    uint32_t s0 = b.s0 << 2, s1 = b.s1 << 2, s2 = b.s2 << 2, s3 = b.s3 << 2;
-    const uint32_t f0 = b.f0 << 2, f1 = b.f1 << 2, f2 = b.f2 << 2, f3 = b.f3 << 2;
-    const uint32_t c = x + o0;
-    const uint4 wa = philox(c, t, 0u, kStreamMet, a.key0, a.key1);
-    const uint4 wb = philox(c, t, 1u, kStreamMet, a.key0, a.key1);
-    const uint32_t p23 = (1u << s2) + (1u << s3);
-    met_arm<Q>(s0, p23 + (1u << s1) + (8u << f0), wa.x, wa.y, tbl, wsum);
-    met_arm<Q>(s1, p23 + (1u << s0) + (8u << f1), wa.z, wa.w, tbl, wsum);
-    const uint32_t p01 = (1u << s0) + (1u << s1);
-    met_arm<Q>(s2, p01 + (1u << s3) + (8u << f2), wb.x, wb.y, tbl, wsum);
-    met_arm<Q>(s3, p01 + (1u << s2) + (8u << f3), wb.z, wb.w, tbl, wsum);
-    st8(rs, s0 >> 2, x, o0);
-    st8(rs, s1 >> 2, x, N + o0);
-    st8(rs, s2 >> 2, x, 2 * N + o0);
-    st8(rs, s3 >> 2, x, 3 * N + o0);
-}
-
 // ---------------------------------------------------------------------------
-// Quad variant: lane j owns the four columns 4j..4j+3 and moves whole dwords
+// Column quads: lane j owns the four columns 4j..4j+3 and moves whole dwords
 // of every plane.  In a row of parity P the updated cells sit at bytes P and
 // P+2 of the quad; their x neighbours are the other bytes of the same dwords
 // except one, fetched with a single byte load (the column left of the quad
@@ -294,8 +246,8 @@ __device__ __forceinline__ void met_reduce(uint32_t wsum, int64_t* bank, uint32_
     // Exact while the 10-bit fields hold the sums: a cell's four moves change
     // N_sigma of its six arm pairs by at most 6 and N_HB_raw of its four links
     // by at most 4 in all, so |sum dc| <= 6 and |sum dh| <= 4 per cell, and a
-    // lane moves at most 64 cells per launch (32 rows of a column quad, or 64
-    // rows of a column pair): |sum dc| <= 384, |sum dh| <= 256, accepted <= 256.
+    // lane moves at most 64 cells per launch (32 rows of a column quad):
+    // |sum dc| <= 384, |sum dh| <= 256, accepted <= 256.
     const int ws = (int)wsum;
     const int sdc = (ws << 22) >> 22;
     const int r1v = (ws - sdc) >> 10;
@@ -311,25 +263,23 @@ __device__ __forceinline__ void met_reduce(uint32_t wsum, int64_t* bank, uint32_
 // through its rows lets the laggards catch up: all waves stay resident until
 // the last quarter of the pass.  it: the wave's row-pair index, n: its count.
 // (Batched passes, whose workgroups belong to lattices of different sizes,
-// measured faster without it: ON = false.)
-template <bool ON>
+// measured faster without it.)
 struct ProgressPrio {
     uint32_t t1, t2, t3;                      // first row-pair index of levels 2, 1, 0
     __device__ __forceinline__ explicit ProgressPrio(uint32_t n)
         : t1((n + 3) / 4), t2((2 * n + 3) / 4), t3((3 * n + 3) / 4)
     {
-        if (ON) __builtin_amdgcn_s_setprio(3);
+        __builtin_amdgcn_s_setprio(3);
     }
     __device__ __forceinline__ void step(uint32_t it) const
     {
-        if (!ON) return;
         if (it == t1) __builtin_amdgcn_s_setprio(2);
         if (it == t2) __builtin_amdgcn_s_setprio(1);
         if (it == t3) __builtin_amdgcn_s_setprio(0);
     }
 };
 
-// No occupancy cap: the quad loop needs ~84 VGPRs (5 wavefronts per SIMD).
+// No occupancy cap: the quad loop needs 66..82 VGPRs (5..7 wavefronts per SIMD).
 // Caps measured slower (64 VGPRs for 7 wavefronts without spills, or 8 with
 // a small spill).  At L = 4096 the host picks 16 rows per wavefront: 1024
 // workgroups, all resident at once.
@@ -386,7 +336,7 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs 
             else met_quad<Q, PE, R, LE>(a, rs, tb, t, y0, x4, cur, wsum, ragged);
         }
     } else if (active) {
-        const ProgressPrio<true> prio((y1 - y0) >> 1);
+        const ProgressPrio prio((y1 - y0) >> 1);
         for (uint32_t y = y0; y < y1; y += 2) {
             prio.step((y - y0) >> 1);
             const QuadBytes odd = met_load4<PO, R>(a, rs, y + 1, x4, x4h, xl, xr);
@@ -397,67 +347,6 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs 
         }
     }
     met_reduce(wsum, a.slots + KAPPA * kBankSlots, blockIdx.x + blockIdx.y * gridDim.x);
-}
-
-// Byte-lane variant (any even L): lane i owns the column pair (2i, 2i+1).
-template <int Q, bool PRIO>
-__device__ __forceinline__ uint32_t met_byte_block(const LatticeArgs& a, uint2* tbl, uint32_t t, int theta,
-                                                   int colour, uint32_t bx, uint32_t by)
-{
-    const uint32_t L = a.L, half = L >> 1;
-    const uint32_t lane = threadIdx.x & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t pair = bx * 64 + lane;
-    const uint32_t y0 = (by * 4 + wave) * a.rows;    // even
-    const bool active = pair < half && y0 < L;
-    // column of the updated cell in even rows (A) and odd rows (B), and its x neighbours
-    const uint32_t xA = 2 * pair + colour, xB = 2 * pair + (1 - colour);
-    const uint32_t xpA = (xA + 1 == L) ? 0 : xA + 1, xmA = (xA == 0) ? L - 1 : xA - 1;
-    const uint32_t xpB = (xB + 1 == L) ? 0 : xB + 1, xmB = (xB == 0) ? L - 1 : xB - 1;
-    const uint32_t y1 = min(y0 + a.rows, L);            // y1 - y0 is even
-    const __amdgpu_buffer_rsrc_t rs = sigma_rsrc(a.sigma, 4 * a.N);
-    // Software pipeline: the loads of the next row are issued before the
-    // current row is computed.  They never alias its stores: the current
-    // row writes only cells of the updated colour, the next row reads its
-    // own (different) cells and facing arms of the other colour.
-    CellBytes cur = {};
-    if (active) cur = met_load(a, rs, y0, xA, xpA, xmA);
-    met_table(a, tbl, theta);
-    uint32_t wsum = 0;
-    if (active) {
-        const ProgressPrio<PRIO> prio((y1 - y0) >> 1);
-        for (uint32_t y = y0; y < y1; y += 2) {
-            prio.step((y - y0) >> 1);
-            const CellBytes odd = met_load(a, rs, y + 1, xB, xpB, xmB);
-            met_cell<Q>(a, rs, tbl, t, y, xA, cur, wsum);
-            const uint32_t yn = (y + 2 < y1) ? y + 2 : y;     // last pair: a harmless re-read
-            cur = met_load(a, rs, yn, xA, xpA, xmA);
-            met_cell<Q>(a, rs, tbl, t, y + 1, xB, odd, wsum);
-        }
-    }
-    return wsum;
-}
-
-template <int Q>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void met_sweep_kernel(LatticeArgs a, VolArgs va, StepCtl ctl,
-                                                                                                             int colour)
-{
-    if (blockIdx.y == a.row_blocks) {
-        __shared__ double term[40];
-        if (blockIdx.x == 0 && threadIdx.x < 64) open_next(va, term, a.st->view + (ctl.bank ^ 1u));
-        return;
-    }
-    StepView* view = a.st->view + ctl.bank;
-    const int skip = view->skip;
-    int theta = colour == 0 ? view->theta : view->theta2;
-    const uint32_t t = view->t_cur;
-    if (skip) return;                                      // step limit reached
-    if (colour == 0 && view->pending) theta = resolve_step(va, view, false, blockIdx.x + blockIdx.y == 0);
-    // 32 entries: indices d + 16 for d in -15..15, so that even out-of-range
-    // bond indices (a caller-supplied configuration) cannot read outside it.
-    __shared__ uint2 tbl[32];
-    const uint32_t wsum = met_byte_block<Q, true>(a, tbl, t, theta, colour, blockIdx.x, blockIdx.y);
-    met_reduce(wsum, a.slots + colour * kBankSlots, blockIdx.x + blockIdx.y * gridDim.x);
 }
 
 // The chain c of workgroup b in a batched launch: start[c] <= b < start[c + 1]
