@@ -245,6 +245,7 @@ void chain_setup(const cvf_params* p, uint8_t* d_sigma, char* work, size_t work_
         a.rows = one ? 1 : m.rows;
         a.row_blocks = one ? (a.L + 3) / 4 : m.row_blocks;
     }
+    a.sw_through = a.N <= kSwThroughCells;
     a.met_le = 1;                        // every threshold >= 1: acceptance is word <= thr - 1
     for (int th = 0; th < 2; ++th)
         for (int i = 0; i < 21; ++i)
@@ -527,6 +528,8 @@ int batch_upload(cvf_batch* b, hipStream_t s, uint8_t* staging)
     b->start.assign(count + 1, 0);
     b->tstart.assign(count + 1, 0);
     uint32_t total = 0, ttotal = 0;
+    uint64_t cells = 0;
+    for (const cvf_state* st : b->chains) cells += st->N;
     for (uint32_t c = 0; c < count; ++c) {
         const cvf_state* st = b->chains[c];
         BatchEntry& e = b->host[c];
@@ -534,6 +537,7 @@ int batch_upload(cvf_batch* b, hipStream_t s, uint8_t* staging)
         e.la = st->la;
         // batched passes move quads, two-cell ones at the row ends of L % 4 == 2
         e.la.quad = (e.la.L % 4 == 0) ? 1u : 2u;
+        e.la.sw_through = cells <= kSwThroughCells;
         e.va = st->va;
         e.va.mode = kVolMet;
         e.va.met_att_add = 4 * (int64_t)st->N;

@@ -115,6 +115,18 @@ constexpr size_t sw_bytes_of(uint64_t L)
 // An exchange word that names no link (flat indices are at most 4N - 1 <= 2^32 - 2).
 constexpr uint32_t kNoLink = 0xFFFFFFFFu;
 
+// Cells in a launch (of all its chains) up to which the tile kernel writes its
+// local roots through L2.  Their 8 bytes per cell then fit the eight L2s (32 MB),
+// and written through they need not leave them when the launch ends.  With
+// more cells they leave during the launch anyway, and the lines that two tiles
+// share (their rows start off a line boundary) are better merged there than
+// sent out twice.  us per step, through / left to L2: L = 1414 41.0 / 41.9,
+// L = 2046 73.0 / 73.5, L = 2048 69.1 / 71.0, L = 2150 86.1 / 84.4, L = 3000
+// 145.8 / 142.5, L = 4098 310 / 297, L = 8190 1226 / 1152 (L = 2352 92.9 /
+// 93.6, L = 8192 1117 / 1112); batches of L = 1024 and 1022: four chains 75.1 /
+// 74.6, five 97.1 / 94.1, 32 608 / 587.
+constexpr uint64_t kSwThroughCells = 1ull << 22;
+
 // The allocation-free entry point keeps a whole Swendsen-Wang workspace for
 // lattices up to kNoAllocMaxL in one fixed device array.
 constexpr uint32_t kNoAllocMaxL = 512;
@@ -147,6 +159,7 @@ struct LatticeArgs {
     uint32_t rows;           // Metropolis: rows per wavefront (1, or even, <= 32)
     uint32_t row_blocks;     // Metropolis: grid.y
     uint32_t quad;           // Metropolis, 4-column lanes: 1 = L % 4 == 0, 2 = L % 4 == 2
+    uint32_t sw_through;     // Swendsen-Wang: 1 up to kSwThroughCells in the launch
     uint32_t met_le;         // 1: no Metropolis threshold is 0, so acceptance is one compare (word <= thr - 1)
 };
 

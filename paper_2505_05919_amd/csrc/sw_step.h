@@ -404,9 +404,11 @@ __device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const VolArgs
             const __amdgpu_buffer_rsrc_t rl = buf_rsrc(a.lroot + (size_t)p * N, 2 * N);
             if (qp.n == 4) {
                 const u32x2 w = {eb[0] | eb[1] << 16, eb[2] | eb[3] << 16};
-                __builtin_amdgcn_raw_buffer_store_b64(w, rl, (int)(2 * qp.c), 0, kThrough);
+                if (a.sw_through) __builtin_amdgcn_raw_buffer_store_b64(w, rl, (int)(2 * qp.c), 0, kThrough);
+                else __builtin_amdgcn_raw_buffer_store_b64(w, rl, (int)(2 * qp.c), 0, 0);
             } else if (qp.n) {
-                __builtin_amdgcn_raw_buffer_store_b32(eb[0] | eb[1] << 16, rl, (int)(2 * qp.c), 0, kThrough);
+                if (a.sw_through) __builtin_amdgcn_raw_buffer_store_b32(eb[0] | eb[1] << 16, rl, (int)(2 * qp.c), 0, kThrough);
+                else __builtin_amdgcn_raw_buffer_store_b32(eb[0] | eb[1] << 16, rl, (int)(2 * qp.c), 0, 0);
             }
 #pragma unroll
             for (uint32_t j = 0; j < 4; ++j)

@@ -298,3 +298,19 @@ def test_batch_across_the_liquid_limit(cvf, algo):
         assert digest(x) == digest(y), L
         assert x.obs() == y.obs(), L
     b.close()
+
+
+@pytest.mark.parametrize("count", [4, 5])
+def test_batch_sw_either_side_of_the_cache_limit(cvf, count):
+    """What the tile kernel writes through L2 follows from the cells of the
+    whole batch: four chains of L = 1024 stay below the limit, five do not."""
+    mk = lambda k: cvf.Chain(cvf.cvf_params_from_si(290.0, 0.1, L=1024 if k else 1022, seed=80 + k))
+    alone, chains = [mk(k) for k in range(count)], [mk(k) for k in range(count)]
+    for ch in alone:
+        ch.sw(3)
+    b = cvf.Batch(chains).sw(3)
+    for x, y in zip(alone, chains):
+        assert digest(x) == digest(y)
+        assert x.obs() == y.obs()
+        assert (x.labels() == y.labels()).all()
+    b.close()

@@ -318,3 +318,11 @@ def test_sw_tiles_at_their_edges(cvf, oracle_mod, L, q):
     the tile's own; rows off a dword boundary; first, last and single tiles."""
     op = oracle_mod.params_from_si(260.0, 0.1, L=L, q=q, seed=1500 + L + q)
     run_pair(cvf, oracle_mod, op, [("sw", 1), ("sw", 3), ("met", 1), ("sw", 2)], labels=True)
+
+
+@pytest.mark.parametrize("L", [2048, 2050, 2052])
+def test_sw_local_roots_either_side_of_the_cache_limit(cvf, oracle_mod, L):
+    """The largest lattice whose local roots are written through L2 and the
+    first ones whose roots are left there, with whole and two-cell row ends."""
+    op = oracle_mod.params_from_si(280.0, 0.1, L=L, seed=1700 + L)
+    run_pair(cvf, oracle_mod, op, [("sw", 2)], labels=True)
