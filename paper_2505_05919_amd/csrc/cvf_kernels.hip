@@ -5,6 +5,7 @@
 // and the workgroup, int64 atomics into spread slots.  The single-wave
 // volume kernel is the only floating-point code (FP64, no contraction).
 #include "cvf_internal.h"
+#include "met_launch.h"
 
 #include <atomic>
 #include <type_traits>
@@ -414,18 +415,22 @@ hipError_t launch_volume(const VolArgs& a, hipStream_t s, DispatchEvents ev)
 
 // A launch that opens the next step has one more row of workgroups, whose
 // first one does it.
-template <int Q, bool R, bool LE>
+template <int Q, bool R, bool LE, int POLICY = kThrough>
 hipError_t launch_quad_r(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, dim3 grid, hipStream_t s,
                          const DispatchEvents& ev)
 {
-    if (colour == 0) return go(met_sweep4_kernel<Q, 0, R, LE>, grid, dim3(256), s, ev, a, v, c);
-    return go(met_sweep4_kernel<Q, 1, R, LE>, grid, dim3(256), s, ev, a, v, c);
+    if (colour == 0) return go(met_sweep4_kernel<Q, 0, R, LE, POLICY>, grid, dim3(256), s, ev, a, v, c);
+    return go(met_sweep4_kernel<Q, 1, R, LE, POLICY>, grid, dim3(256), s, ev, a, v, c);
 }
 
 template <int Q>
 hipError_t launch_quad(const LatticeArgs& a, const VolArgs& v, StepCtl c, int colour, dim3 grid, hipStream_t s,
                        const DispatchEvents& ev)
 {
+    if (a.quad == 2 && !met_through(a.L)) {
+        if (a.met_le) return launch_quad_r<Q, true, true, kPlain>(a, v, c, colour, grid, s, ev);
+        return launch_quad_r<Q, true, false, kPlain>(a, v, c, colour, grid, s, ev);
+    }
     if (a.quad == 2) {
         if (a.met_le) return launch_quad_r<Q, true, true>(a, v, c, colour, grid, s, ev);
         return launch_quad_r<Q, true, false>(a, v, c, colour, grid, s, ev);

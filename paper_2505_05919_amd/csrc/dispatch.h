@@ -22,7 +22,7 @@ namespace cvf {
 // bond masks) and the cubic shifts stay plain stores: written through, batches of
 // column-pair lattices went from 58 to 60 us and the cubic step from 126.0 to
 // 127.4.
-constexpr int kThrough = 17;
+constexpr int kThrough = 17, kPlain = 0;
 
 // Null events: a plain launch.
 struct DispatchEvents {

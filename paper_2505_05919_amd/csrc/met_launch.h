@@ -60,4 +60,13 @@ inline MetShape met_shape(uint32_t L)
 #endif
 inline bool met_one_row(uint32_t L) { return L <= CVF_MET_ONE_ROW_MAX; }
 
+// Whether a sweep's stores are written through L2.  Rows of L % 4 == 2 start
+// off a dword boundary, so that a wavefront's stores end inside a line: on
+// lattices well beyond the L2s' 32 MB those lines are better merged there than
+// sent out in two parts (us per sweep, through / left to L2: L = 2050 37.4 /
+// 38.4, L = 3002 57.7 / 61.2, L = 3602 80.0 / 80.3, L = 4094 93.8 / 90.9, L =
+// 4098 102.2 / 99.7, L = 8002 327.8 / 318.5, L = 8194 367.5 / 355.9, L = 16382
+// 1305 / 1288).  Aligned rows gain or stay the same at every size.
+inline bool met_through(uint32_t L) { return L % 4 == 0 || (uint64_t)L * L <= 14000000u; }
+
 }  // namespace cvf

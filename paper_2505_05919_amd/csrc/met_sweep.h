@@ -95,14 +95,16 @@ __device__ __forceinline__ uint32_t ld32(__amdgpu_buffer_rsrc_t r, uint32_t voff
     return __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0);
 }
 
+template <int POLICY = kThrough>
 __device__ __forceinline__ void st32(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)voff, (int)soff, kThrough);
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)voff, (int)soff, POLICY);
 }
 
+template <int POLICY>
 __device__ __forceinline__ void st16(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, kThrough);
+    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, POLICY);
 }
 
 // Dword of a quad in a row that may start two bytes past a dword boundary: the
@@ -115,11 +117,11 @@ __device__ __forceinline__ uint32_t ld32r(__amdgpu_buffer_rsrc_t r, uint32_t vof
     return __builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
 }
 
-template <bool R>
+template <bool R, int POLICY>
 __device__ __forceinline__ void st32r(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff, uint32_t soff, bool ragged)
 {
-    if (!R || !ragged) st32(r, v, voff, soff);
-    else st16(r, v, voff, soff);
+    if (!R || !ragged) st32<POLICY>(r, v, voff, soff);
+    else st16<POLICY>(r, v, voff, soff);
 }
 
 struct QuadBytes {
@@ -164,7 +166,8 @@ __device__ __forceinline__ uint32_t put2(uint32_t d, uint32_t v1, uint32_t v2)
     return (d & keep) | w1 | (v2 << (8 * B2 - 2));
 }
 
-template <int Q, int P, bool R, bool LE = false, bool VROW = false>
+// POLICY: cache policy of the stores.
+template <int Q, int P, bool R, bool LE = false, bool VROW = false, int POLICY = kThrough>
 __device__ __forceinline__ void met_quad(const LatticeArgs& a, __amdgpu_buffer_rsrc_t rs, const uint2* tbl,
                                          uint32_t t, uint32_t y, uint32_t x4, const QuadBytes& q, uint32_t& wsum,
                                          bool ragged)
@@ -209,10 +212,10 @@ __device__ __forceinline__ void met_quad(const LatticeArgs& a, __amdgpu_buffer_r
     if (R && ragged) wsum = wkeep;
     using RS = RowSplit<VROW>;
     const uint32_t xv = RS::v(x4, o0);
-    st32r<R>(rs, put2<B1, B2>(q.d0, a0, b0), xv, RS::s(0, o0), ragged);
-    st32r<R>(rs, put2<B1, B2>(q.d1, a1, b1), xv, RS::s(N, o0), ragged);
-    st32r<R>(rs, put2<B1, B2>(q.d2, a2, b2), xv, RS::s(2 * N, o0), ragged);
-    st32r<R>(rs, put2<B1, B2>(q.d3, a3, b3), xv, RS::s(3 * N, o0), ragged);
+    st32r<R, POLICY>(rs, put2<B1, B2>(q.d0, a0, b0), xv, RS::s(0, o0), ragged);
+    st32r<R, POLICY>(rs, put2<B1, B2>(q.d1, a1, b1), xv, RS::s(N, o0), ragged);
+    st32r<R, POLICY>(rs, put2<B1, B2>(q.d2, a2, b2), xv, RS::s(2 * N, o0), ragged);
+    st32r<R, POLICY>(rs, put2<B1, B2>(q.d3, a3, b3), xv, RS::s(3 * N, o0), ragged);
 }
 
 // Entry i (0..63) of the two-theta table: theta = i / 32, index d + 16 with
@@ -288,7 +291,7 @@ struct ProgressPrio {
 // chain state, so the table entries of both theta values and the first row
 // are requested before the state (skip flag, theta, step) is read, and the
 // first wait covers all three at once.
-template <int Q, int KAPPA, bool R, bool LE>
+template <int Q, int KAPPA, bool R, bool LE, int POLICY>
 __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs va, StepCtl ctl)
 {
     __shared__ __align__(16) uint2 tbl[64];
@@ -332,18 +335,18 @@ __global__ __launch_bounds__(256) void met_sweep4_kernel(LatticeArgs a, VolArgs 
     uint32_t wsum = 0;
     if (one) {
         if (active) {
-            if (y0 & 1) met_quad<Q, PO, R, LE>(a, rs, tb, t, y0, x4, cur, wsum, ragged);
-            else met_quad<Q, PE, R, LE>(a, rs, tb, t, y0, x4, cur, wsum, ragged);
+            if (y0 & 1) met_quad<Q, PO, R, LE, false, POLICY>(a, rs, tb, t, y0, x4, cur, wsum, ragged);
+            else met_quad<Q, PE, R, LE, false, POLICY>(a, rs, tb, t, y0, x4, cur, wsum, ragged);
         }
     } else if (active) {
         const ProgressPrio prio((y1 - y0) >> 1);
         for (uint32_t y = y0; y < y1; y += 2) {
             prio.step((y - y0) >> 1);
             const QuadBytes odd = met_load4<PO, R>(a, rs, y + 1, x4, x4h, xl, xr);
-            met_quad<Q, PE, R, LE>(a, rs, tb, t, y, x4, cur, wsum, ragged);
+            met_quad<Q, PE, R, LE, false, POLICY>(a, rs, tb, t, y, x4, cur, wsum, ragged);
             const uint32_t yn = (y + 2 < y1) ? y + 2 : y;
             cur = met_load4<PE, R>(a, rs, yn, x4, x4h, xl, xr);
-            met_quad<Q, PO, R, LE>(a, rs, tb, t, y + 1, x4, odd, wsum, ragged);
+            met_quad<Q, PO, R, LE, false, POLICY>(a, rs, tb, t, y + 1, x4, odd, wsum, ragged);
         }
     }
     met_reduce(wsum, a.slots + KAPPA * kBankSlots, blockIdx.x + blockIdx.y * gridDim.x);

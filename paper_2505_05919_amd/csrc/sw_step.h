@@ -405,10 +405,10 @@ __device__ __forceinline__ void sw_tile_body(const LatticeArgs& a, const VolArgs
             if (qp.n == 4) {
                 const u32x2 w = {eb[0] | eb[1] << 16, eb[2] | eb[3] << 16};
                 if (a.sw_through) __builtin_amdgcn_raw_buffer_store_b64(w, rl, (int)(2 * qp.c), 0, kThrough);
-                else __builtin_amdgcn_raw_buffer_store_b64(w, rl, (int)(2 * qp.c), 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b64(w, rl, (int)(2 * qp.c), 0, kPlain);
             } else if (qp.n) {
                 if (a.sw_through) __builtin_amdgcn_raw_buffer_store_b32(eb[0] | eb[1] << 16, rl, (int)(2 * qp.c), 0, kThrough);
-                else __builtin_amdgcn_raw_buffer_store_b32(eb[0] | eb[1] << 16, rl, (int)(2 * qp.c), 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b32(eb[0] | eb[1] << 16, rl, (int)(2 * qp.c), 0, kPlain);
             }
 #pragma unroll
             for (uint32_t j = 0; j < 4; ++j)

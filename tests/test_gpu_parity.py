@@ -326,3 +326,13 @@ def test_sw_local_roots_either_side_of_the_cache_limit(cvf, oracle_mod, L):
     first ones whose roots are left there, with whole and two-cell row ends."""
     op = oracle_mod.params_from_si(280.0, 0.1, L=L, seed=1700 + L)
     run_pair(cvf, oracle_mod, op, [("sw", 2)], labels=True)
+
+
+@pytest.mark.parametrize("L", [3738, 3742])
+def test_metropolis_either_side_of_the_store_policy(cvf, oracle_mod, L):
+    """The largest L % 4 == 2 lattice whose sweeps write through L2 and the
+    first one whose sweeps do not; at 60 K some moves are never accepted, which
+    takes the two-compare acceptance."""
+    for q, T in ((4, 60.0), (6, 300.0)):
+        op = oracle_mod.params_from_si(T, 0.1, L=L, q=q, seed=1800 + L + q)
+        run_pair(cvf, oracle_mod, op, [("met", 1)], algo_mask=1)
