@@ -541,9 +541,9 @@ hipError_t recount_launch(const LatticeArgs& a, int64_t* out, int spread, const 
     const uint32_t blocks = (sh.quads + kBlock - 1) / kBlock;
     const uint32_t most = OBS ? kRecountBlocks : 2048u;
     const uint32_t grid = blocks < most ? blocks : most;
-    if (a.L % 4 == 0) recount_kernel<4, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
-    else if (a.L % 2 == 0) recount_kernel<2, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
-    else recount_kernel<1, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
+    if (a.L % 4 == 0) recount_kernel<0, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
+    else if (a.L > 4) recount_kernel<1, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
+    else recount_kernel<2, OBS><<<grid, kBlock, 0, s>>>(a, sh, out, spread, o);
     return hipGetLastError();
 }
 

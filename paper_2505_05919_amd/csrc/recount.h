@@ -13,17 +13,22 @@ struct RecountShape {
     double inv_row;                // 1 / per_row
 };
 
-// n bytes from p (AL: 4, 2 or 1, the alignment of p; n < 4 only at a row's
-// end), the others zero.
-template <int AL>
+// The n bytes of a quad at p, the others zero.  MODE 0: L % 4 == 0, an aligned
+// dword.  1: other L > 4, a dword at any byte address, which the loads take; the
+// last quad of a row (n < 4) reads the row's last dword and shifts it, so that
+// no access leaves the row.  2: L = 2, 3, single bytes.  (With rows of L % 4 == 2
+// in half words and odd rows in single bytes the observables took 1.34 and 2.27
+// ms at L = 16382 and 16383, now 0.57; L = 16384 takes 0.55.)
+template <int MODE>
 __device__ __forceinline__ uint32_t row_bytes(const uint8_t* p, uint32_t n)
 {
-    if (AL == 4) return *(const uint32_t*)p;
-    if (AL == 2) return *(const uint16_t*)p | (n > 2 ? (uint32_t)*(const uint16_t*)(p + 2) << 16 : 0u);
-    uint32_t w = p[0];
-#pragma unroll
-    for (uint32_t j = 1; j < 4; ++j)
-        if (j < n) w |= (uint32_t)p[j] << (8 * j);
+    if (MODE == 0) return *(const uint32_t*)p;
+    uint32_t w = 0;
+    if (MODE == 1) {
+        __builtin_memcpy(&w, p - (4 - n), 4);
+        return w >> (8 * (4 - n));
+    }
+    for (uint32_t j = 0; j < n; ++j) w |= (uint32_t)p[j] << (8 * j);
     return w;
 }
 
@@ -38,7 +43,7 @@ __device__ __forceinline__ uint32_t zero_flags(uint32_t x)
 // which the workgroup that arrives last writes the record (Eq. (1), (3)).
 // Values are counted exactly for any byte.  Bound by reading 4 bytes per cell
 // and by ~250 VALU instructions per quad.
-template <int AL, bool OBS>
+template <int MODE, bool OBS>
 __global__ __launch_bounds__(kBlock) void recount_kernel(LatticeArgs a, RecountShape sh, int64_t* out, int spread,
                                                          ObsArgs o)
 {
@@ -52,11 +57,11 @@ __global__ __launch_bounds__(kBlock) void recount_kernel(LatticeArgs a, RecountS
         const uint32_t x = 4 * j, n = min(4u, L - x);
         const uint32_t row = y * L, rowp = (y + 1 == L) ? 0u : row + L;
         const uint8_t* c = s + row + x;
-        const uint32_t w[4] = {row_bytes<AL>(c, n), row_bytes<AL>(c + N, n), row_bytes<AL>(c + 2 * N, n),
-                               row_bytes<AL>(c + 3 * N, n)};
+        const uint32_t w[4] = {row_bytes<MODE>(c, n), row_bytes<MODE>(c + N, n),
+                               row_bytes<MODE>(c + 2 * N, n), row_bytes<MODE>(c + 3 * N, n)};
         const uint32_t nx = s[N + row + (x + n == L ? 0u : x + n)];       // arm 1 right of the quad
         const uint32_t f0 = (w[1] >> 8) | (nx << (8 * (n - 1)));
-        const uint32_t f2 = row_bytes<AL>(s + 3 * N + rowp + x, n);
+        const uint32_t f2 = row_bytes<MODE>(s + 3 * N + rowp + x, n);
         const uint32_t have = 0x01010101u >> (8 * (4 - n));
         v[0] += __popc(zero_flags(w[0] ^ f0) & have) + __popc(zero_flags(w[2] ^ f2) & have);
 #pragma unroll
