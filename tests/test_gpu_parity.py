@@ -336,3 +336,18 @@ def test_metropolis_either_side_of_the_store_policy(cvf, oracle_mod, L):
     for q, T in ((4, 60.0), (6, 300.0)):
         op = oracle_mod.params_from_si(T, 0.1, L=L, q=q, seed=1800 + L + q)
         run_pair(cvf, oracle_mod, op, [("met", 1)], algo_mask=1)
+
+
+@pytest.mark.parametrize("L", [2, 3, 5, 64, 724, 725, 1023, 1448, 2049, 8191])
+def test_state_counts_of_every_length(cvf, L):
+    """Added to what the counters hold, for word counts with and without a
+    remainder, below and above one and two loads of four words per lane."""
+    import torch
+    p = cvf.cvf_params_from_si(300.0, 0.1, L=L, seed=1900 + L)
+    ch = cvf.Chain(p, cvf.CVF_ALGO_METROPOLIS)
+    want = torch.bincount(ch.sigma.to(torch.int32), minlength=6)
+    got = torch.arange(6, dtype=torch.int64, device="cuda")
+    for _ in range(2):
+        cvf.cvf_state_counts(ch.h, got.data_ptr())
+    assert (got == 2 * want + torch.arange(6, device="cuda")).all()
+    ch.close()
