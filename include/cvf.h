@@ -286,7 +286,8 @@ int cvf_batch_create_async(cvf_state *const *chains, int32_t count, void *d_desc
 /* Launch shape of the batched Metropolis pass: a chain's colour pass is cut
  * into work units of two rows times a column quad, numbered row-pair major,
  * and a lane moves `rows` / 2 consecutive-by-64 units, i.e. `rows` rows (even,
- * 2..32); 0 restores the default (2).
+ * 2..32); 0 restores the default (2, or 4 where the batch has more than 2^25
+ * cells).
  * Invalidates captured graphs.  Re-uploads the descriptor table on stream
  * and waits for the copy. */
 int cvf_batch_set_rows(cvf_batch *b, int32_t rows, void *stream);

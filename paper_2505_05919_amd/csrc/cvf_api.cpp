@@ -43,9 +43,14 @@ namespace {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Rows per lane of a batched Metropolis pass before the autotuner runs (256
-// replicas of L 64..512: 2 / 4 / 6 / 8 rows 90 / 100 / 98 / 101 us per sweep).
-constexpr uint32_t kBatchDefaultRows = 2;
+// Rows per lane of a batched Metropolis pass before the autotuner runs: two, in
+// batches of more than 2^25 cells four, where a lane's fixed work counts and
+// not the wavefronts to choose from.  us per sweep at two / four rows: 256
+// replicas of L = 64..512 (17e6 cells) 90 / 100, 32 of L = 1024 and 1022 (33e6)
+// 172 / 170, 256 of L = 512 and 510 (67e6) 355 / 335, four of L = 4096 (67e6)
+// 345 / 316.
+constexpr uint64_t kBatchManyCells = 1ull << 25;
+inline uint32_t batch_default_rows(uint64_t cells) { return cells > kBatchManyCells ? 4u : 2u; }
 
 int validate(const cvf_params* p)
 {
@@ -546,7 +551,7 @@ int batch_upload(cvf_batch* b, hipStream_t s, uint8_t* staging)
         e.upr_inv = 1.0 / (double)e.upr;
         e.units = e.upr * (Lc / 2);
         // the tuned parameter: a lane moves `rows` rows (rows / 2 units of two rows)
-        const uint32_t rows = b->rows > 0 ? (uint32_t)b->rows : kBatchDefaultRows;
+        const uint32_t rows = b->rows > 0 ? (uint32_t)b->rows : batch_default_rows(cells);
         e.iters = rows / 2 < 1 ? 1 : rows / 2;
         e.blocks = (uint32_t)(((uint64_t)e.units + 256ull * e.iters - 1) / (256ull * e.iters));
         b->start[c] = total;

@@ -314,3 +314,18 @@ def test_batch_sw_either_side_of_the_cache_limit(cvf, count):
         assert x.obs() == y.obs()
         assert (x.labels() == y.labels()).all()
     b.close()
+
+
+@pytest.mark.parametrize("Ls", [[4096, 4094], [4096, 4096, 66]])
+def test_batch_default_rows_either_side_of_the_limit(cvf, Ls):
+    """The default rows per lane follow from the cells of the whole batch (up
+    to 2^25 and more): the trajectories are those of the chains alone."""
+    mk = lambda L: cvf.Chain(cvf.cvf_params_from_si(290.0, 0.1, L=L, seed=90 + L), cvf.CVF_ALGO_METROPOLIS)
+    alone, chains = [mk(L) for L in Ls], [mk(L) for L in Ls]
+    for ch in alone:
+        ch.metropolis(3)
+    b = cvf.Batch(chains).metropolis(3)
+    for x, y in zip(alone, chains):
+        assert digest(x) == digest(y)
+        assert x.obs() == y.obs()
+    b.close()
