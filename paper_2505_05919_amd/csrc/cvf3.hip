@@ -701,18 +701,7 @@ struct cvf3_state {
 
 namespace {
 
-size_t al256(size_t n) { return (n + 255) & ~(size_t)255; }
-
-size_t ws3_bytes(const cvf_params* p, int algo_mask)
-{
-    size_t b = al256(sizeof(Dev3State)) + al256(sizeof(int64_t) * kAcc * kSlots) +
-               al256(sizeof(int64_t) * kRc * kSlots) + al256(sizeof(Tab3));
-    if (algo_mask & CVF_ALGO_SW) {
-        const size_t N = (size_t)p->L * p->L * p->L;
-        b += al256(N * sizeof(uint32_t)) + al256(6 * N * sizeof(uint32_t));
-    }
-    return b;
-}
+constexpr size_t al256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 // Tiles of a cluster update: 8 x 8 x 4 cells, one per thread, where the chip
 // has wavefronts to spare and the latency of a workgroup decides (a step takes
@@ -721,7 +710,7 @@ size_t ws3_bytes(const cvf_params* p, int algo_mask)
 // and wider loads.
 using Sw3Big = Tile3<16, 8, 8, 4>;
 using Sw3Small = Tile3<8, 8, 4, 1>;
-bool sw3_big(uint64_t L) { return L >= 80; }
+constexpr bool sw3_big(uint64_t L) { return L >= 80; }
 
 // Plus nodes of the tiling (as many minus nodes): a face layer of L^2 per tile
 // along each axis.
@@ -730,7 +719,36 @@ constexpr size_t tile_nodes(uint64_t L)
 {
     return (size_t)(((L + TL::TX - 1) / TL::TX + (L + TL::TY - 1) / TL::TY + (L + TL::TZ - 1) / TL::TZ) * L * L);
 }
-size_t sw3_nodes(uint64_t L) { return sw3_big(L) ? tile_nodes<Sw3Big>(L) : tile_nodes<Sw3Small>(L); }
+constexpr size_t sw3_nodes(uint64_t L) { return sw3_big(L) ? tile_nodes<Sw3Big>(L) : tile_nodes<Sw3Small>(L); }
+
+// What a cluster update keeps for F plus nodes and N cells: parents and keys of
+// the nodes, a local root per bond index, a byte per plus node.  A workspace
+// has 28 N bytes for it (see cvf3_workspace_bytes): the tiles above have few
+// enough faces for that at every L, most nearly at L = 4 with 1584 of 1792 bytes.
+constexpr size_t sw3_need(uint64_t L)
+{
+    return sw3_nodes(L) * (4 * sizeof(uint32_t) + 1) + 6 * L * L * L * sizeof(uint16_t);
+}
+constexpr size_t sw3_room(uint64_t L)
+{
+    return al256(L * L * L * sizeof(uint32_t)) + al256(6 * L * L * L * sizeof(uint32_t));
+}
+constexpr uint64_t kSw3MaxL = 894;                         // 6 N < 2^32
+constexpr bool sw3_fits()
+{
+    for (uint64_t L = 2; L <= kSw3MaxL; L += 2)
+        if (sw3_need(L) > sw3_room(L)) return false;
+    return true;
+}
+static_assert(sw3_fits(), "the cluster update's arrays exceed the workspace");
+
+size_t ws3_bytes(const cvf_params* p, int algo_mask)
+{
+    size_t b = al256(sizeof(Dev3State)) + al256(sizeof(int64_t) * kAcc * kSlots) +
+               al256(sizeof(int64_t) * kRc * kSlots) + al256(sizeof(Tab3));
+    if (algo_mask & CVF_ALGO_SW) b += sw3_room((uint64_t)p->L);
+    return b;
+}
 
 // r3(m): integer points on the sphere i^2 + j^2 + k^2 = m, counted as
 // octant points with signs (each nonzero coordinate doubles the count).
@@ -974,7 +992,7 @@ extern "C" {
 int validate_algo3(const cvf_params* p, int algo_mask)
 {
     if (algo_mask & ~(CVF_ALGO_METROPOLIS | CVF_ALGO_SW)) return CVF_EINVAL;
-    if ((algo_mask & CVF_ALGO_SW) && 6ull * (uint64_t)p->L * p->L * p->L >= (1ull << 32)) return CVF_EINVAL;
+    if ((algo_mask & CVF_ALGO_SW) && (uint64_t)p->L > kSw3MaxL) return CVF_EINVAL;
     return CVF_OK;
 }
 

@@ -268,3 +268,51 @@ def test_cvf3_state_counts_series(c3, oracle_mod, algo):
         want.append(oc.obs()["count"])
     assert np.array_equal(got, np.asarray(want, dtype=np.int64))
     ch.close()
+
+
+@pytest.mark.parametrize("L", [258, 892, 894])
+def test_cvf3_sw_large_sampled(c3, oracle_mod, L):
+    """Cluster steps up to the largest lattice (6N < 2^32), on sampled cells:
+    every label is a root not above its index, the two ends of every link that
+    the oracle's words activate share it, every bond index moved by the shift of
+    its cluster, and the counters equal the full recount."""
+    import torch
+    from paper_2505_05919_amd import cvf
+    op = oracle_mod.params_from_si(210.0, 0.1, L=L, seed=5300 + L)
+    say(f"case sw large L={L}")
+    _, sw = oracle_mod.tables(op)
+    thr_s, thr_e = int(sw[0]), int(sw[2])                  # cooperative, covalent in the liquid
+    N, L2 = L ** 3, L * L
+    ch = c3.Chain3(gpu_params(cvf, op), algo_mask=cvf.CVF_ALGO_SW)
+    rng = np.random.default_rng(L)
+    xyz = [(x, y, z) for x in (0, 15, 16, L - 1) for y in (0, 7, 8, L - 1) for z in (0, L - 1)]
+    xyz += [tuple(int(w) for w in r) for r in rng.integers(0, L, size=(250, 3))]
+    flat = lambda x, y, z: (x % L) + L * ((y % L) + L * (z % L))
+    at = lambda t, i: t[torch.tensor(i, dtype=torch.int64, device="cuda")].cpu().numpy()
+    cells = [flat(*p) for p in xyz]
+    nbrs = [[flat(x + 1, y, z), flat(x, y + 1, z), flat(x, y, z + 1)] for x, y, z in xyz]
+    idx = [b * N + c for c in cells for b in range(6)]
+    old = at(ch.sigma, idx)
+    facing = at(ch.sigma, [(2 * d + 1) * N + n[d] for n in nbrs for d in range(3)]).reshape(-1, 3)
+    ch.sw(1)
+    assert ch.obs()["consistent"] == 1
+    lab = ch.labels()
+    eta = at(ch.eta, [d * N + c for c in cells for d in range(3)]).reshape(-1, 3)
+    pairs = []
+    for c, n, s, f, e in zip(cells, nbrs, old.reshape(-1, 6), facing, eta):
+        w = [int(v) for b in range(5) for v in oracle_mod.philox([c, 0, b, 3], op.seed)]
+        pairs += [(2 * d * N + c, (2 * d + 1) * N + n[d]) for d in range(3) if s[2 * d] == f[d] and e[d] and w[d] < thr_e]
+        arms = [(i, j) for i in range(6) for j in range(i + 1, 6)]
+        pairs += [(i * N + c, j * N + c) for k, (i, j) in enumerate(arms) if s[i] == s[j] and w[3 + k] < thr_s]
+    l = at(lab, idx).view(np.uint32).astype(np.int64)
+    assert (l <= np.array(idx)).all()
+    assert np.array_equal(at(lab, l).view(np.uint32).astype(np.int64), l), "labels must be roots"
+    assert len(pairs) > 500
+    a, b = (at(lab, [p[k] for p in pairs]) for k in (0, 1))
+    assert np.array_equal(a, b), "both ends of an active link share the label"
+    shift = np.array([oracle_mod.sw_shift(op, int(r), 0) for r in l])
+    assert np.array_equal(at(ch.sigma, idx), (old + shift) % op.q)
+    del lab
+    ch.close()
+    del ch
+    torch.cuda.empty_cache()
