@@ -205,6 +205,13 @@ struct StepCtl {
     uint32_t bank, open;
 };
 
+// Workgroups of a batched launch that open the next step of `count` chains, one
+// wavefront each, and the chain of wavefront w of the b-th of them (none if it
+// is count or more).  waves: wavefronts per workgroup of the launch.
+constexpr uint32_t kMetWaves = 4, kSwWaves = kTT / 64;
+constexpr uint32_t open_blocks(uint32_t count, uint32_t waves) { return (count + waves - 1) / waves; }
+constexpr uint32_t open_chain(uint32_t b, uint32_t w, uint32_t waves) { return waves * b + w; }
+
 // Launchers (cvf_kernels.hip).  Each returns the launch status.
 hipError_t launch_state_init(DevState* st, int64_t* slots, const DevTables* tab, double v_init, hipStream_t s);
 hipError_t launch_set_stop(DevState* st, int64_t stop_at, hipStream_t s);

@@ -615,20 +615,17 @@ hipError_t launch_sw_counters_init(const LatticeArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-// Workgroups that open the next step of `count` chains, one wavefront each.
-inline uint32_t open_blocks(uint32_t count, StepCtl c) { return c.open ? (count + 3) / 4 : 0; }
-
 template <int Q>
 void launch_batch_q(BatchEntry* ent, const uint32_t* start, uint32_t count, uint32_t total, int colour, int le,
                     StepCtl c, hipStream_t s)
 {
-    const uint32_t grid = total + open_blocks(count, c);
+    const uint32_t grid = total + (c.open ? open_blocks(count, kMetWaves) : 0u);
     if (le) {
-        if (colour == 0) met_batch_kernel<Q, 0, true><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
-        else met_batch_kernel<Q, 1, true><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
+        if (colour == 0) met_batch_kernel<Q, 0, true><<<grid, 64 * kMetWaves, 0, s>>>(ent, ent, start, count, total, c);
+        else met_batch_kernel<Q, 1, true><<<grid, 64 * kMetWaves, 0, s>>>(ent, ent, start, count, total, c);
     } else {
-        if (colour == 0) met_batch_kernel<Q, 0, false><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
-        else met_batch_kernel<Q, 1, false><<<grid, 256, 0, s>>>(ent, ent, start, count, total, c);
+        if (colour == 0) met_batch_kernel<Q, 0, false><<<grid, 64 * kMetWaves, 0, s>>>(ent, ent, start, count, total, c);
+        else met_batch_kernel<Q, 1, false><<<grid, 64 * kMetWaves, 0, s>>>(ent, ent, start, count, total, c);
     }
 }
 
@@ -656,7 +653,9 @@ hipError_t launch_sw_batch(BatchEntry* ent, const uint32_t* start, uint32_t coun
 {
     if (total_blocks == 0) return hipSuccess;
     if (stage == 0) sw_tile_batch_kernel<<<total_blocks, kTT, 0, s>>>(ent, start, count, c);
-    else sw_flip_batch_kernel<<<total_blocks + open_blocks(count, c), kTT, 0, s>>>(ent, start, count, total_blocks, c);
+    else
+        sw_flip_batch_kernel<<<total_blocks + (c.open ? open_blocks(count, kSwWaves) : 0u), kTT, 0, s>>>(
+            ent, start, count, total_blocks, c);
     return hipGetLastError();
 }
 

@@ -424,7 +424,7 @@ __device__ __forceinline__ void batch_units(const LatticeArgs& a, uint2* tbl, in
 // Batches are mostly small lattices: the 8-wavefront occupancy measured
 // faster than the uncapped register budget.
 template <int Q, int KAPPA, bool LE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void met_batch_kernel(
+__global__ __launch_bounds__(64 * kMetWaves) __attribute__((amdgpu_waves_per_eu(8, 8))) void met_batch_kernel(
     const BatchEntry* __restrict__ ent, BatchEntry* wr, const uint32_t* __restrict__ start, uint32_t count,
     uint32_t total, StepCtl ctl)
 {
@@ -432,9 +432,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // theta2 of a pending step, which this launch does not read); the entry
     // itself is read through ent, with scalar loads
     __shared__ uint2 tbl[32];
-    if (KAPPA == 1 && blockIdx.x >= total) {               // opens the next step of four chains
-        __shared__ double term[4][40];
-        const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = 4 * (blockIdx.x - total) + w;
+    if (KAPPA == 1 && blockIdx.x >= total) {               // opens the next step of a chain per wavefront
+        __shared__ double term[kMetWaves][40];
+        const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = open_chain(blockIdx.x - total, w, kMetWaves);
         if (c < count) open_next(ent[c].va, term[w], wr[c].view + (ctl.bank ^ 1u));
         return;
     }

@@ -782,8 +782,9 @@ __global__ __launch_bounds__(kTT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     StepCtl ctl)
 {
     __shared__ __align__(16) FlipLds lds;
-    if (blockIdx.x >= total) {                // opens the next step of four chains
-        const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = 4 * (blockIdx.x - total) + w;
+    static_assert(sizeof(FlipLds) >= kSwWaves * 40 * sizeof(double), "the shell terms of each wavefront's step");
+    if (blockIdx.x >= total) {                // opens the next step of a chain per wavefront
+        const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = open_chain(blockIdx.x - total, w, kSwWaves);
         if (i >= count) return;
         VolArgs v = ent[i].va;
         v.mode = kVolSw;
