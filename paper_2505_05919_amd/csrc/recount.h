@@ -82,14 +82,19 @@ __global__ __launch_bounds__(kBlock) void recount_kernel(LatticeArgs a, RecountS
         return;
     }
     block_add<8>(v, dst, spread);
-    // The additions act at the device-coherent level; they are complete before
-    // the arrival is counted, and the last workgroup reads the sums there.
-    __builtin_amdgcn_s_waitcnt(0);
+    // The workgroup's additions come before its arrival (the barrier and the
+    // arrival's release), and the last workgroup reads the sums after it has
+    // seen every arrival (its acquire, which the others do without: it would
+    // invalidate the L2 they read the lattice through).  The release costs
+    // nothing up to L = 2048 and 3.5 us of 69 at L = 4096; an acquire in every
+    // workgroup took 2.5 us at L = 1024 and 5 at L = 4096.
     __syncthreads();
     __shared__ uint32_t last;
-    if (threadIdx.x == 0) last = atomicAdd(&o.obs->arrived, 1u) + 1 == gridDim.x ? 1u : 0u;
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(&o.obs->arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
     __syncthreads();
     if (!last || threadIdx.x != 0) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     int64_t acc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
