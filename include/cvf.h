@@ -65,7 +65,8 @@ extern "C" {
 
 /* cvf_params.flags */
 #define CVF_NO_VOLUME_MOVE  1u  /* skip the volume move of every step        */
-#define CVF_KEEP_SIGMA      2u  /* cvf_init keeps the caller's sigma          */
+#define CVF_KEEP_SIGMA      2u  /* cvf_init keeps the caller's sigma, every
+                                   byte of which must be below q             */
 
 /* Reduced units: energies in eps = 5.5 kJ/mol, volumes in v0 = r0^3
  * (Table I).  beta = eps/(k_B T N_A); P is P r0^3 N_A / eps. */

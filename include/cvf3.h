@@ -88,8 +88,11 @@ int cvf3_workspace_bytes(const cvf_params *p, int algo_mask, size_t *bytes);
 int cvf3_tables(const cvf_params *p, uint32_t met[2][3][11], uint32_t eta[9], uint32_t match[9]);
 
 /* Creates a chain: sets v_iso = v_init, draws sigma and eta from the seed
- * (or keeps the caller's when p->flags has CVF_KEEP_SIGMA; eta must then be
- * a valid state: every cube's eta = 0 edges a perfect matching), and counts
+ * (or keeps the caller's when p->flags has CVF_KEEP_SIGMA: every byte of
+ * sigma must then be below q, every byte of eta 0 or 1, and eta a valid
+ * state: every cube's eta = 0 edges a perfect matching; the kernels decide
+ * four cells on packed bytes, and other values change their neighbours'
+ * moves), and counts
  * N_HB_raw and N_sigma.  Synchronises the stream.  Errors: CVF_EINVAL
  * (parameters, NULL or misaligned pointers), CVF_ENOMEM (work_bytes too
  * small or host allocation), CVF_EHIP. */

@@ -472,10 +472,13 @@ __global__ __launch_bounds__(kBlock) void eta3_pair_kernel(Lat3 a, EtaShape sh)
     const uint32_t ch = s0 / (2 * sh.chunk), in = s0 - 2 * sh.chunk * ch, par = in >= sh.chunk ? 1u : 0u;
     const uint32_t local = sh.chunk * ch + in - par * sh.chunk, blk = run * sh.per + local;
     if (local >= sh.per || blk >= sh.blocks) return;
-    __shared__ uint32_t match[9], thr[9];
+    // matchings, then the thresholds of dn = -4..4 from word 13 on: dn is in
+    // -12..12 whatever a kept eta holds, which stays inside
+    __shared__ uint32_t match[32];
+    uint32_t* const thr = match + 17;
     if (threadIdx.x < 9) {
         match[threadIdx.x] = a.tab->match[threadIdx.x];
-        thr[threadIdx.x] = a.tab->eta[threadIdx.x];
+        match[13 + threadIdx.x] = a.tab->eta[threadIdx.x];
     }
     __syncthreads();
     const uint32_t r = blk * kBlock + threadIdx.x;
@@ -535,7 +538,7 @@ __global__ __launch_bounds__(kBlock) void eta3_pair_kernel(Lat3 a, EtaShape sh)
             const uint32_t half = 0xFFFu << (16 * c);
             const uint32_t to = (~match[m < 0 ? 0 : m] << (16 * c)) & half, eq = ~unlike & half;
             const int dn = __popc(to & eq) - __popc(old & eq);
-            const uint32_t lim = theta ? thr[dn + 4] : 0xFFFFFFFFu;
+            const uint32_t lim = theta ? thr[dn] : 0xFFFFFFFFu;
             const bool acc = m >= 0 && (lim == 0xFFFFFFFFu || rnd.y < lim);
             neu = acc ? (neu & ~half) | to : neu;
             cnt[0] += acc && a.eta_hb ? dn : 0;

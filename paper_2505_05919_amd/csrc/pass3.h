@@ -229,8 +229,10 @@ __global__ __launch_bounds__(kBlock) void pass3_kernel(Lat3 a_, PassShape sh)
     const uint32_t s0 = a.pass ? (ends >> (8 * (a.pass - 1))) & 0xFFu : 0u, s1 = (ends >> (8 * a.pass)) & 0xFFu;
     if (s0 == s1) return;
     // 3 words unused, then [dh + 1][dc + 5] for theta eta = 1, then [dc + 5]
-    // for theta eta = 0
-    __shared__ uint32_t tab[47];
+    // for theta eta = 0, then unused ones, so that a move's byte offset (see
+    // pass_move) stays inside whatever bytes a kept configuration holds
+    __shared__ uint32_t tab[64];
+    static_assert(sizeof(tab) > 0xFF, "every byte offset lies in the table");
     if (threadIdx.x >= 3 && threadIdx.x < 47) {
         const uint32_t k = threadIdx.x - 3;
         const uint32_t thr = k < 33 ? (&a.tab->met[1][0][0])[k] : a.tab->met[0][1][k - 33];
