@@ -244,11 +244,10 @@ void chain_setup(const cvf_params* p, uint8_t* d_sigma, char* work, size_t work_
     a.met_invd = 1.0 / (double)dm;
     a.flip_invd = 1.0 / (double)dq;
     {
-        const MetShape m = met_shape(a.L);
-        a.quad = a.L % 4 == 0 ? 1 : 2;
-        const bool one = met_one_row(a.L);
-        a.rows = one ? 1 : m.rows;
-        a.row_blocks = one ? (a.L + 3) / 4 : m.row_blocks;
+        const MetShape m = met_launch(a.L);
+        a.quad = m.quad;
+        a.rows = m.rows;
+        a.row_blocks = m.row_blocks;
     }
     a.sw_through = a.N <= kSwThroughCells;
     a.met_le = 1;                        // every threshold >= 1: acceptance is word <= thr - 1

@@ -16,14 +16,14 @@ namespace cvf {
 
 struct MetShape {
     uint32_t quad;         // 1: 4-column quads (L % 4 == 0), 2: quads, L % 4 == 2, 0: column pairs
-    uint32_t rows;         // rows per wavefront (even, 2..32)
+    uint32_t rows;         // rows per wavefront (1, or even, 2..32)
     uint32_t row_blocks;   // grid.y: four wavefronts per workgroup stack vertically
 };
 
-// Lanes own 4-column quads (the last one ragged in mode 2) or column pairs
-// (mode 0), 64 per wavefront; each wavefront walks `rows` rows of its column
-// group.  The row count aims the grid at CVF_MET_WAVES wavefronts (at
-// L = 4096: 16 rows, 1024 workgroups, all resident at once).
+// Row blocks: lanes own 4-column quads (the last one ragged in mode 2) or
+// column pairs (mode 0), 64 per wavefront; each wavefront walks `rows` rows of
+// its column group.  The row count aims the grid at CVF_MET_WAVES wavefronts
+// (at L = 4096: 16 rows, 1024 workgroups, all resident at once).
 inline MetShape met_shape_mode(uint32_t L, uint32_t quad)
 {
     MetShape m;
@@ -41,8 +41,8 @@ inline MetShape met_shape_mode(uint32_t L, uint32_t quad)
     return m;
 }
 
-// The launch shape of a single chain in row blocks.  (Smaller L % 4 == 2
-// lattices have one in column pairs, which is not launched: see below.)
+// Row blocks of any lattice, small ones of L % 4 == 2 in column pairs.  What a
+// launch takes is met_launch.
 inline MetShape met_shape(uint32_t L)
 {
     const uint32_t quad = (L % 4 == 0) ? 1 : (L >= CVF_MET_RAGGED_MIN ? 2 : 0);
@@ -50,7 +50,7 @@ inline MetShape met_shape(uint32_t L)
 }
 
 // Largest side whose lattice is moved one row of quads per wavefront instead of
-// by the shape above: up to there the launch is bound by a wavefront's latency,
+// in row blocks: up to there the launch is bound by a wavefront's latency,
 // not by issue (us per sweep, one row / shape above: L = 256 8.9 / 10.3,
 // L = 1024 11.5 / 13.2, L = 1536 16.7 / 20.5, L = 2048 24.5 / 24.3,
 // L = 4096 79.1 / 72.9; against column pairs L = 66 9.1 / 10.4, L = 258
@@ -59,6 +59,14 @@ inline MetShape met_shape(uint32_t L)
 #define CVF_MET_ONE_ROW_MAX 2046
 #endif
 inline bool met_one_row(uint32_t L) { return L <= CVF_MET_ONE_ROW_MAX; }
+
+// The shape of a launch: quads, one row or a block of rows per wavefront.
+inline MetShape met_launch(uint32_t L)
+{
+    const uint32_t quad = L % 4 == 0 ? 1 : 2;
+    if (met_one_row(L)) return {quad, 1, (L + 3) / 4};
+    return met_shape_mode(L, quad);
+}
 
 // Whether a sweep's stores are written through L2.  Rows of L % 4 == 2 start
 // off a dword boundary, so that a wavefront's stores end inside a line: on
