@@ -80,7 +80,7 @@ struct Lat3 {
     uint32_t L, N, h, q;
     uint32_t key0, key1;
     uint32_t pass;
-    uint32_t quad;            // 1: L % 4 == 0, four cells per lane; 0: cell pairs
+    uint32_t quad;            // 1: L % 4 == 0, quads of four cells; 0: the last quad of a row has two
     uint32_t eta_hb;          // 1: the eta move adds its change of N_HB_raw to the counters
     double   invL, invH, invQ4, Nd, beta, J, P, vHB, dv_max;
     int32_t  do_volume;
@@ -588,12 +588,6 @@ __global__ __launch_bounds__(kBlock) void eta3_pair_kernel(Lat3 a, EtaShape sh)
         if (sm) atomicAdd((unsigned long long*)(a.slots + (size_t)slot * kSlots + blockIdx.x % kSlots),
                           (unsigned long long)sm);
     }
-}
-
-// 0x01 in every byte of x that is zero, 0x00 elsewhere (no carry crosses a byte).
-__device__ __forceinline__ uint32_t zero_bytes(uint32_t x)
-{
-    return (~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu)) >> 7;
 }
 
 #include "pass3.h"

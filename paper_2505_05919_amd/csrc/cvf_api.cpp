@@ -220,8 +220,7 @@ void chain_setup(const cvf_params* p, uint8_t* d_sigma, char* work, size_t work_
     build_tables(p, &st->htab);
 
     const double Jeff = p->J - p->P * p->vHB;
-    const uint32_t qm1 = (uint32_t)p->q - 1;
-    const uint64_t dm = (1ull << 32) / qm1, dq = (1ull << 32) / (uint32_t)p->q;
+    const uint64_t dq = (1ull << 32) / (uint32_t)p->q;
     LatticeArgs& a = st->la;
     a.sigma = d_sigma;
     a.st = st->dst;
@@ -238,10 +237,8 @@ void chain_setup(const cvf_params* p, uint8_t* d_sigma, char* work, size_t work_
     a.key0 = (uint32_t)p->seed;
     a.key1 = (uint32_t)(p->seed >> 32);
     a.q = (uint32_t)p->q;
-    a.met_lim = (uint32_t)(qm1 * dm - 1);
     a.flip_lim = (uint32_t)((uint64_t)p->q * dq - 1);
     a.jeff_sign = Jeff > 0.0 ? 1 : (Jeff < 0.0 ? -1 : 0);
-    a.met_invd = 1.0 / (double)dm;
     a.flip_invd = 1.0 / (double)dq;
     {
         const MetShape m = met_launch(a.L);

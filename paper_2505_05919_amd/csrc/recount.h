@@ -32,12 +32,6 @@ __device__ __forceinline__ uint32_t row_bytes(const uint8_t* p, uint32_t n)
     return w;
 }
 
-// 0x01 in every zero byte of x, 0x00 elsewhere (no carry crosses a byte).
-__device__ __forceinline__ uint32_t zero_flags(uint32_t x)
-{
-    return (~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu)) >> 7;
-}
-
 // N_HB_raw and N_sigma of the lattice added to out[0 / 1][spread] (OBS =
 // false), or with the state counts to the observables' accumulators, from
 // which the workgroup that arrives last writes the record (Eq. (1), (3)).
@@ -63,16 +57,16 @@ __global__ __launch_bounds__(kBlock) void recount_kernel(LatticeArgs a, RecountS
         const uint32_t f0 = (w[1] >> 8) | (nx << (8 * (n - 1)));
         const uint32_t f2 = row_bytes<MODE>(s + 3 * N + rowp + x, n);
         const uint32_t have = 0x01010101u >> (8 * (4 - n));
-        v[0] += __popc(zero_flags(w[0] ^ f0) & have) + __popc(zero_flags(w[2] ^ f2) & have);
+        v[0] += __popc(zero_bytes(w[0] ^ f0) & have) + __popc(zero_bytes(w[2] ^ f2) & have);
 #pragma unroll
         for (int p = 0; p < 4; ++p)
 #pragma unroll
-            for (int q = p + 1; q < 4; ++q) v[1] += __popc(zero_flags(w[p] ^ w[q]) & have);
+            for (int q = p + 1; q < 4; ++q) v[1] += __popc(zero_bytes(w[p] ^ w[q]) & have);
         if (OBS) {
 #pragma unroll
             for (int p = 0; p < 4; ++p)
 #pragma unroll
-                for (uint32_t k = 0; k < 6; ++k) v[2 + k] += __popc(zero_flags(w[p] ^ (k * 0x01010101u)) & have);
+                for (uint32_t k = 0; k < 6; ++k) v[2 + k] += __popc(zero_bytes(w[p] ^ (k * 0x01010101u)) & have);
         }
     }
     int64_t* dst = out + (blockIdx.x & (spread - 1));

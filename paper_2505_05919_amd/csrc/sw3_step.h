@@ -590,21 +590,6 @@ __global__ __launch_bounds__(kBlock) void sw3_union_kernel(Lat3 a, uint32_t nx, 
     uf_unite(a.par, a.key, pu, pv);
 }
 
-// Exclusive prefix sum over the wavefront of per-lane values c < 32, and its
-// total: one ballot per bit.
-__device__ __forceinline__ uint32_t wave_excl_scan5(uint32_t c, uint32_t& total)
-{
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (uint32_t b = 0; b < 5; ++b) {
-        const uint64_t m = __ballot((c >> b) & 1u);
-        pre += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) << b;
-        tot += (uint32_t)__popcll(m) << b;
-    }
-    total = tot;
-    return pre;
-}
-
 // Shift of the cluster with label r: pick(word 0 of Philox(r, t, 0, SWF), q),
 // NONE -> 0.
 __device__ __forceinline__ uint32_t cluster_shift(const Lat3& a, uint32_t r, uint32_t t)

@@ -173,10 +173,10 @@ __device__ __forceinline__ uint32_t tile_global(const TileGeom& g, uint32_t L, u
 // right are the next lane's, and a plane's four sigma are one dword and its
 // four local roots two; rows start at even addresses, which wider accesses take.
 // Against one bond index per lane and access (16 byte and 16 half-word loads
-// or stores, and the new sigma through LDS twice) the flip went from 20.4 to
-// 17.3 us at L = 1414, from 8.8 to 6.5 us at L = 256 and from 35.4 to 29.2 us
-// for 100 mixed lattices; the tile kernel stayed at 25.5 us, of which its 340
-// VALU instructions per cell take 17 at full issue rate.
+// or stores, and the new sigma through LDS twice) the flip, with its stores
+// written through, went from 19.7 to 15.0 us at L = 1414 and from 8.7 to 6.7 us
+// at L = 256; the tile kernel from 25.2 to 24.2 us, of which its 340 VALU
+// instructions per cell take 17 at full issue rate.
 struct QuadPos {
     uint32_t lx, ly, lc;  // first cell: tile column, tile row, local index (4 threadIdx.x)
     uint32_t c;           // its global index (0 if none is inside)
@@ -514,21 +514,6 @@ struct FlipLds {
     uint32_t nroot, nrootb;
 };
 static_assert(kTH % 4 == 0, "four columns of the bottom edge's facing arms are one aligned word");
-
-// Exclusive prefix sum over the wavefront of per-lane values c < 32, and
-// its total: one ballot per bit.
-__device__ __forceinline__ uint32_t wave_excl_scan5(uint32_t c, uint32_t& total)
-{
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (uint32_t b = 0; b < 5; ++b) {
-        const uint64_t m = __ballot((c >> b) & 1u);
-        pre += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) << b;
-        tot += (uint32_t)__popcll(m) << b;
-    }
-    total = tot;
-    return pre;
-}
 
 __device__ __forceinline__ void sw_flip_body(const LatticeArgs& a, uint32_t bank, const TileGeom& g, FlipLds& lds)
 {
