@@ -236,7 +236,10 @@ int cvf_tables(const cvf_state *st, uint32_t met[2][3][7], uint64_t sw[3]);
  * cvf_kernel_times synchronises those events and returns, for kind k, the
  * number of launches and their mean duration in ms since timing was
  * enabled. */
-#define CVF_K_VOLUME    0   /* volume move / counter fold          */
+#define CVF_K_VOLUME    0   /* counter fold + volume move of a call's
+                               first step; later steps are opened
+                               inside the last launch of the step
+                               before them, in that launch's time   */
 #define CVF_K_MET_SWEEP 1   /* one checkerboard colour sweep       */
 #define CVF_K_SW_BONDS  2   /* bond activation + in-tile labels
                                + the tile-crossing unions          */
@@ -255,8 +258,9 @@ int cvf_destroy(cvf_state *st);
 
 /* ---------------------------------------------------------------------------
  * Batched execution: many independent chains advanced together, one launch
- * per colour phase for all of them (plus one volume launch with a wavefront
- * per chain).  Every chain computes exactly what cvf_metropolis_sweeps
+ * per colour phase for all of them (and per call, or per graph replay, one
+ * volume launch with a wavefront per chain, which opens the first step; later
+ * steps are opened inside the phase before them).  Every chain computes exactly what cvf_metropolis_sweeps
  * computes for it alone (same Philox keying, same update order), so results
  * are identical alone and in the batch.
  * ------------------------------------------------------------------------- */

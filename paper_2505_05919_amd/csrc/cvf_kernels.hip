@@ -543,8 +543,10 @@ hipError_t launch_met_domain(const LatticeArgs& a, const VolArgs& v, StepCtl c, 
 {
     // lanes own column quads; rows per lane for at most 5000 wavefronts, up to
     // 8 (a lane's 10-bit counter fields take 170 moves, a row has up to 8).
-    // Measured, us per sweep: one / two rows 20.5 / 21.0 at L = 1025 (4126
-    // wavefronts of one row) and 28.9 / 25.2 at L = 1414 (7821); two / four
+    // Measured, us per sweep: one / two rows 20.5 / 21.3 at L = 1025 (4126
+    // wavefronts of one row), 19.5 / 20.6 at L = 1128 (4970), 20.6 / 20.8 at
+    // L = 1160 (5256), 24.1 / 23.2 at L = 1203 (5657), 22.5 / 23.4 at L = 1300
+    // (6602) and 28.7 / 25.4 at L = 1414 (7821); two / four
     // 34.9 / 33.9 at L = 2048; four / eight / sixteen 97.1 / 94.3 / 99.2 at
     // L = 4096
     const uint64_t quads = (a.L + 3) / 4;

@@ -18,10 +18,13 @@ namespace cvf {
 // runs beside the launch's arithmetic instead.  Measured: Metropolis sweeps at
 // L = 2048 / 4096 28.3 / 76.8 -> 25.0 / 74.2 us, a Swendsen-Wang step at
 // L = 1414 45.3 -> 42.8 us, cubic passes at 260^3 152.8 -> 151.0 us (sc1 alone
-// the same, nt no change).  Single bytes per lane (the ends of ragged rows,
-// bond masks) and the cubic shifts stay plain stores: written through, batches of
-// column-pair lattices went from 58 to 60 us and the cubic step from 126.0 to
-// 127.4.
+// the same, nt no change).  It costs traffic: a line that a launch completes in
+// parts goes out in parts (191 MB per batched colour pass of 256 replicas
+// instead of 167, 50 MB per tile launch at L = 1414 instead of 44), which large
+// lattices pay for.  So unaligned Metropolis rows (met_through) and the tiles'
+// local roots (kSwThroughCells) are written through only up to a size, and
+// single bytes per lane (the ends of ragged rows, bond masks) and the cubic
+// shifts not at all (a cubic cluster step 127.4 us with them, 126.0 without).
 constexpr int kThrough = 17, kPlain = 0;
 
 // Null events: a plain launch.

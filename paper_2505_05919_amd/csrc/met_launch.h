@@ -52,9 +52,10 @@ inline MetShape met_shape(uint32_t L)
 // Largest side whose lattice is moved one row of quads per wavefront instead of
 // in row blocks: up to there the launch is bound by a wavefront's latency,
 // not by issue (us per sweep, one row / shape above: L = 256 8.9 / 10.3,
-// L = 1024 11.5 / 13.2, L = 1536 16.7 / 20.5, L = 2048 24.5 / 24.3,
-// L = 4096 79.1 / 72.9; against column pairs L = 66 9.1 / 10.4, L = 258
-// 10.1 / 11.1, L = 1022 12.4 / 18.9).
+// L = 1024 11.6 / 13.1, L = 1600 18.9 / 21.4, L = 1900 23.7 / 25.9, L = 2044
+// 25.2 / 26.3, L = 2046 26.5 / 30.8, L = 2048 24.6 / 24.5, L = 2400 34.0 / 33.0,
+// L = 4096 79.1 / 72.9; sides that are no multiple of 16 would still gain up to
+// 2200, L = 2050 29.3 / 36.6).
 #ifndef CVF_MET_ONE_ROW_MAX
 #define CVF_MET_ONE_ROW_MAX 2046
 #endif
