@@ -667,8 +667,8 @@ def main():
         "frac": round(achieved_gbs / HBM_PEAK_GBS, 4),
         "traffic": traffic,
         "alg_bytes_per_update": 2,
-        "limiter": "VALU issue, not HBM: see alu (the fraction of the 8 TB/s roofline is what the path reaches; "
-                   "the integer work per update caps it well below 1)",
+        "limiter": "VALU issue: see alu (39 instructions per update at 91 % of the full-rate peak inside a launch; "
+                   "the integer work per update caps the fraction of the 8 TB/s roofline well below 1)",
         "alu": {"achieved": round(achieved_tops, 2), "peak": round(VALU_PEAK_TOPS, 2),
                 "unit": "T lane-ops/s (full-rate 32-bit VALU issue)",
                 "frac": round(achieved_tops / VALU_PEAK_TOPS, 4), "ops_per_update_floor": ALU_OPS_PER_UPDATE,
